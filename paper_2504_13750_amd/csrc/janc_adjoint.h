@@ -242,17 +242,15 @@ __device__ __forceinline__ void cell_speeds_of(const AdjGrid& g, CMech* m, const
         sy = fabs(vy) + cs;
     } else {
         constexpr int NS = NU - 3;
-        const double rho = u[0], ir = 1.0 / rho;
+        const double rho = u[0], ir = quotient(1.0, rho);
         const double vx = u[1] * ir, vy = u[2] * ir;
         double Y[NS];
         mass_fractions<NU>(u, ir, Y);
-        MixNasa x;
-        mix_nasa<NS>(Y, m, x);
         const double T = VT[c];
-        double ec, cv;
-        mix_eval(x, T, ec, cv);
-        const double p = rho * x.Rmix * T;
-        const double gam = (cv + x.Rmix) / cv;
+        double cv, Rmix;
+        mix_cv<NS>(Y, m, T, cv, Rmix);
+        const double p = rho * Rmix * T;
+        const double gam = quotient(cv + Rmix, cv);
         const double cs = sqrt(gam * p * ir);
         sx = fabs(vx) + cs;
         sy = fabs(vy) + cs;

@@ -16,6 +16,18 @@ typedef __attribute__((address_space(4))) const DevMech CMech;
 typedef __attribute__((address_space(4))) const DevDomain CDom;
 __device__ __forceinline__ CMech* cmech(const DevMech* p) { return (CMech*)p; }
 __device__ __forceinline__ CDom& cdom(const DevDomain* p, int d) { return ((CDom*)p)[d]; }
+typedef __attribute__((address_space(4))) const int CInt;
+template <class T>
+__device__ __forceinline__ T cload(const T* p) {
+    static_assert(sizeof(T) % 4 == 0, "whole words");
+    CInt* w = (CInt*)(const int*)p;
+    union { int i[sizeof(T) / 4]; T t; } v;
+#pragma unroll
+    for (int k = 0; k < (int)(sizeof(T) / 4); ++k) v.i[k] = w[k];
+    return v.t;
+}
+__device__ __forceinline__ DevBlock cblock(const DevBlock* p, int b) { return cload(p + b); }
+__device__ __forceinline__ Tile ctile(const Tile* p, int t) { return cload(p + t); }
 
 // ------------------------------------------------------------------ small helpers
 __device__ __forceinline__ double sq(double x) { return x * x; }
@@ -34,13 +46,40 @@ __device__ __forceinline__ void slot_max(const Reduce& r, int buf, int idx, doub
     atomicMax(&r.buf[slot_word(r.stride, buf, idx)], (unsigned long long)__double_as_longlong(v));
 }
 
+// n / d where d is a normal number and so is its reciprocal: hardware reciprocal (relative
+// error 2^-24 over 1.3e8 random values), one Newton step (2^-48) and one residual step
+// (2^-96 before the last rounding: the rounded quotient, equal to n / d on all of them).
+// Six instructions for the eleven of the general division.
+__device__ __forceinline__ double quotient(double n, double d) {
+    double y = __builtin_amdgcn_rcp(d);
+    y = __builtin_fma(__builtin_fma(-d, y, 1.0), y, y);
+    const double q = n * y;
+    return __builtin_fma(__builtin_fma(-d, q, n), y, q);
+}
+
+// Makes `next` available only once `done` is computed: keeps the compiler from starting the
+// arithmetic on `next` early, whose registers cost more than its parallelism gives.
+__device__ __forceinline__ void after(double& done, double& next) {
+    asm volatile("" : "+v"(done), "+v"(next));
+}
+
+// A value that is the same in every lane, moved to scalar registers.
+__device__ __forceinline__ double uniform(double v) {
+    union { double d; int i[2]; } x;
+    x.d = v;
+    x.i[0] = __builtin_amdgcn_readfirstlane(x.i[0]);
+    x.i[1] = __builtin_amdgcn_readfirstlane(x.i[1]);
+    return x.d;
+}
+
 __device__ __forceinline__ double wave_max(double v) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
     return v;
 }
 
-// Workgroup max of three values; thread 0 publishes them.
+// Workgroup max of three values over NW waves; thread 0 publishes them.
+template <int NW>
 __device__ __forceinline__ void publish_max3(const Reduce& r, int buf, int i0, int i1, int i2,
                                              double v0, double v1, double v2, double* scratch) {
     v0 = wave_max(v0);
@@ -56,7 +95,7 @@ __device__ __forceinline__ void publish_max3(const Reduce& r, int buf, int i0, i
     __syncthreads();
     if (threadIdx.x == 0) {
         double m0 = scratch[0], m1 = scratch[1], m2 = scratch[2];
-        for (int q = 1; q < WG / 64; ++q) {
+        for (int q = 1; q < NW; ++q) {
             m0 = fmax(m0, scratch[3 * q]);
             m1 = fmax(m1, scratch[3 * q + 1]);
             m2 = fmax(m2, scratch[3 * q + 2]);
@@ -65,6 +104,17 @@ __device__ __forceinline__ void publish_max3(const Reduce& r, int buf, int i0, i
         if (m1 > 0.0) slot_max(r, buf, i1, m1);
         if (m2 > 0.0) slot_max(r, buf, i2, m2);
     }
+}
+
+// The same for values staged in LDS (v[k * 256 + thread], k = 0..2): wave k < 3 takes
+// quantity k of all 256 threads, so that one sixth of the exchanges remain.
+__device__ __forceinline__ void publish_staged(const Reduce& r, int buf, int i0, int i1, int i2,
+                                               const double* v) {
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
+    if (w >= 3) return;
+    const double* x = v + 256 * w + l;
+    const double m = wave_max(fmax(fmax(x[0], x[64]), fmax(x[128], x[192])));
+    if (l == 0 && m > 0.0) slot_max(r, buf, w == 0 ? i0 : w == 1 ? i1 : i2, m);
 }
 
 // Coarse-fine ring test for block-local cell (li, lj) (segment masks per side).
@@ -138,7 +188,7 @@ template <int M, int NU, class Dom, class Mech>
 __device__ __forceinline__ void halo_prims(const double (&u)[NU], double T, const Dom& D,
                                            Mech mech, double& vx, double& vy,
                                            double& p) {
-    const double ir = 1.0 / u[0];
+    const double ir = quotient(1.0, u[0]);
     vx = u[1] * ir;
     vy = u[2] * ir;
     if constexpr (M == DETAILED) {
@@ -157,68 +207,68 @@ __device__ __forceinline__ void halo_prims(const double (&u)[NU], double T, cons
     }
 }
 
-// Mixture NASA-7 coefficients (Y fixed, so the species sums are formed once): per mass,
-// sum_k Y_k R_k a_q of each range, and R_mix. With two NASA-7 ranges (one t_mid for all
-// species) both sets are formed and an evaluation uses the set of its temperature.
-struct MixNasa {
-    double b[6], h[6];
-    double Rmix, tm;
-    bool two;
+// Mixture NASA-7 polynomials (Y fixed, so the species sums are formed once), per mass:
+// e(T) = T (c0 + T (c1 + ..)) + e0 and c_v(T) = c0 + T (v1 + T (v2 + ..)) of one range.
+struct MixPoly {
+    double c0, c1, c2, c3, c4, e0, v1, v2, v3, v4;
 };
 
-template <int NS>
-__device__ __forceinline__ void mix_nasa(const double (&Y)[NS], CMech* m, MixNasa& x) {
-    double b0 = 0.0, b1 = 0.0, b2 = 0.0, b3 = 0.0, b4 = 0.0, b5 = 0.0;
-    double h0 = 0.0, h1 = 0.0, h2 = 0.0, h3 = 0.0, h4 = 0.0, h5 = 0.0;
-    x.two = m->two_range != 0;
-    x.tm = m->tmid[0];
-    x.Rmix = 0.0;
+__device__ __forceinline__ void poly_eval(const MixPoly& x, double T, double& e, double& cv) {
+    e = T * (x.c0 + T * (x.c1 + T * (x.c2 + T * (x.c3 + T * x.c4)))) + x.e0;
+    cv = x.c0 + T * (x.v1 + T * (x.v2 + T * (x.v3 + T * x.v4)));
+}
+
+// Mixture R and the polynomials of one table of coefficients. The coefficients are scalar
+// loads; they are taken three species at a time (all at once they spilled).
+template <int NS, class Tab>
+__device__ __forceinline__ void mix_poly(const double (&Y)[NS], CMech* m, Tab* tab, MixPoly& x, double& Rmix) {
+    double b0 = 0.0, b1 = 0.0, b2 = 0.0, b3 = 0.0, b4 = 0.0, b5 = 0.0, R = 0.0;
 #pragma unroll
     for (int k = 0; k < NS; ++k) {
         const double w = Y[k] * m->Rk[k];
-        x.Rmix += w;
-        b0 += w * m->nasa[k][0];
-        b1 += w * m->nasa[k][1];
-        b2 += w * m->nasa[k][2];
-        b3 += w * m->nasa[k][3];
-        b4 += w * m->nasa[k][4];
-        b5 += w * m->nasa[k][5];
-        if (x.two) {
-            h0 += w * m->nasa_hi[k][0];
-            h1 += w * m->nasa_hi[k][1];
-            h2 += w * m->nasa_hi[k][2];
-            h3 += w * m->nasa_hi[k][3];
-            h4 += w * m->nasa_hi[k][4];
-            h5 += w * m->nasa_hi[k][5];
-        }
+        R += w;
+        b0 += w * tab[k][0];
+        b1 += w * tab[k][1];
+        b2 += w * tab[k][2];
+        b3 += w * tab[k][3];
+        b4 += w * tab[k][4];
+        b5 += w * tab[k][5];
+        if (k % 3 == 2 && k + 1 < NS) asm volatile("" : "+v"(b5), "+s"(m), "+s"(tab));
     }
-    x.b[0] = b0; x.b[1] = b1; x.b[2] = b2; x.b[3] = b3; x.b[4] = b4; x.b[5] = b5;
-    x.h[0] = h0; x.h[1] = h1; x.h[2] = h2; x.h[3] = h3; x.h[4] = h4; x.h[5] = h5;
+    Rmix = R;
+    x.c0 = b0 - R;
+    x.c1 = 0.5 * b1;
+    x.c2 = b2 * (1.0 / 3.0);
+    x.c3 = 0.25 * b3;
+    x.c4 = 0.2 * b4;
+    x.e0 = b5;
+    x.v1 = b1;
+    x.v2 = b2;
+    x.v3 = b3;
+    x.v4 = b4;
 }
 
-// e(T) and cv(T) of the mixture (per mass).
-__device__ __forceinline__ void mix_eval(const MixNasa& x, double Tc, double& ec, double& cvv) {
-    const bool hi = x.two && Tc >= x.tm;
-    const double B0 = hi ? x.h[0] : x.b[0], B1 = hi ? x.h[1] : x.b[1], B2 = hi ? x.h[2] : x.b[2],
-                 B3 = hi ? x.h[3] : x.b[3], B4 = hi ? x.h[4] : x.b[4], B5 = hi ? x.h[5] : x.b[5];
-    const double c0 = B0 - x.Rmix, c1 = 0.5 * B1, c2 = B2 * (1.0 / 3.0), c3 = 0.25 * B3,
-                 c4 = 0.2 * B4;
-    ec = Tc * (c0 + Tc * (c1 + Tc * (c2 + Tc * (c3 + Tc * c4)))) + B5;
-    cvv = c0 + Tc * (B1 + Tc * (B2 + Tc * (B3 + Tc * B4)));
+typedef __attribute__((address_space(4))) const double CNasa[7];
+
+// e(T) and c_v(T) by the range of T.
+__device__ __forceinline__ void range_eval(const MixPoly& lo, const MixPoly& hi, double tm, double T, double& e,
+                                           double& cv) {
+    const bool h = T >= tm;
+    const MixPoly x = {h ? hi.c0 : lo.c0, h ? hi.c1 : lo.c1, h ? hi.c2 : lo.c2, h ? hi.c3 : lo.c3,
+                       h ? hi.c4 : lo.c4, h ? hi.e0 : lo.e0, h ? hi.v1 : lo.v1, h ? hi.v2 : lo.v2,
+                       h ? hi.v3 : lo.v3, h ? hi.v4 : lo.v4};
+    poly_eval(x, T, e, cv);
 }
 
-// Newton for T from the internal energy on the mixture coefficients (Sec. 4.2).
-template <int NS>
-__device__ __forceinline__ unsigned newton_T(const double (&Y)[NS], double e, CMech* m,
-                                             double& T, double& cv, double& Rmix) {
-    MixNasa x;
-    mix_nasa<NS>(Y, m, x);
-    Rmix = x.Rmix;
+// Newton for T: eval(T, e, cv) is the mixture's; cv returns c_v at the root.
+template <class Eval>
+__device__ __forceinline__ unsigned newton_loop(double e, double& T, double& cv, Eval&& eval) {
     unsigned st = STB_NEWTON;
+    double ec;
     for (int it = 0; it < 50; ++it) {
-        double ec, cvv;
-        mix_eval(x, T, ec, cvv);
-        const double dT = (ec - e) / cvv;
+        double cvv;
+        eval(T, ec, cvv);
+        const double dT = quotient(ec - e, cvv);
         T -= dT;
         if (!(fabs(dT) <= 1e-12 * fabs(T))) {
             if (!isfinite(T)) { st = STB_NONFINITE; break; }
@@ -227,9 +277,42 @@ __device__ __forceinline__ unsigned newton_T(const double (&Y)[NS], double e, CM
         st = 0u;
         break;
     }
-    double ec;
-    mix_eval(x, T, ec, cv);
+    eval(T, ec, cv);
     return st;
+}
+
+// Newton for T from the internal energy on the mixture coefficients (Sec. 4.2). With two
+// NASA-7 ranges (one t_mid for all species) both sets are formed and an evaluation uses the
+// set of its temperature.
+template <int NS>
+__device__ __forceinline__ unsigned newton_T(const double (&Y)[NS], double e, CMech* m,
+                                             double& T, double& cv, double& Rmix) {
+    MixPoly lo;
+    mix_poly<NS>(Y, m, (CNasa*)m->nasa, lo, Rmix);
+    if (m->two_range) {
+        MixPoly hi;
+        double R;
+        const double tm = m->tmid[0];
+        mix_poly<NS>(Y, m, (CNasa*)m->nasa_hi, hi, R);
+        return newton_loop(e, T, cv, [&](double Tc, double& ec, double& c) { range_eval(lo, hi, tm, Tc, ec, c); });
+    }
+    return newton_loop(e, T, cv, [&](double Tc, double& ec, double& c) { poly_eval(lo, Tc, ec, c); });
+}
+
+// Mixture R and c_v at a stored temperature, the forward's own sums.
+template <int NS>
+__device__ __forceinline__ void mix_cv(const double (&Y)[NS], CMech* m, double T, double& cv, double& Rmix) {
+    MixPoly lo;
+    double e;
+    mix_poly<NS>(Y, m, (CNasa*)m->nasa, lo, Rmix);
+    if (m->two_range) {
+        MixPoly hi;
+        double R;
+        mix_poly<NS>(Y, m, (CNasa*)m->nasa_hi, hi, R);
+        range_eval(lo, hi, m->tmid[0], T, e, cv);
+    } else {
+        poly_eval(lo, T, e, cv);
+    }
 }
 
 // State of an owned cell after an update: T (closed form or Newton from Tprev),
@@ -241,7 +324,7 @@ __device__ __forceinline__ unsigned owner_state(const double (&u)[NU], double Tp
     const double rho = u[0];
     if (!isfinite(rho)) return STB_NONFINITE;
     if (!(rho > 0.0)) return STB_NEGATIVE;
-    const double ir = 1.0 / rho;
+    const double ir = quotient(1.0, rho);
     vx = u[1] * ir;
     vy = u[2] * ir;
     const double e = u[3] * ir - 0.5 * (vx * vx + vy * vy);
@@ -261,7 +344,7 @@ __device__ __forceinline__ unsigned owner_state(const double (&u)[NU], double Tp
         double cv, Rmix;
         st = newton_T<NS>(Y, e, mech, T, cv, Rmix);
         p = rho * Rmix * T;
-        gam = (cv + Rmix) / cv;
+        gam = quotient(cv + Rmix, cv);
     } else {
         double ee = e;
         if constexpr (M == ONESTEP) ee -= u[4] * ir * D.Q;
@@ -290,7 +373,78 @@ __device__ __forceinline__ double weno5(double a, double b, double c, double d, 
     const double s1 = sq((12.0 * WENO_EPS + 13.0 * t1 * t1) + 3.0 * u1 * u1);
     const double s2 = sq((12.0 * WENO_EPS + 13.0 * t2 * t2) + 3.0 * u2 * u2);
     const double w0 = 0.1 * (s1 * s2), w1 = 0.6 * (s0 * s2), w2 = 0.3 * (s0 * s1);
-    return c + (w0 * r0 + w1 * r1 + w2 * r2) / (6.0 * (w0 + w1 + w2));
+    return c + quotient(w0 * r0 + w1 * r1 + w2 * r2, 6.0 * (w0 + w1 + w2));
+}
+
+// The split fluxes of the detailed model are kept at a sixth of their value, so that the
+// factors 6 of the reconstruction below fall on constants; the other models keep the form
+// above, whose rounding their long runs are compared with.
+template <int M>
+constexpr double SPLIT_SCALE = (M == DETAILED) ? 1.0 / 12.0 : 0.5;
+
+// One-sided WENO5-JS from a..e (a sixth of the split fluxes) as c + num / den: weno5()'s
+// form with everything over 36 * 3 in the smoothness indicators (their common factor
+// cancels in the weights) and the linear weights 1 : 6 : 3.
+__device__ __forceinline__ void weno5_parts(double a, double b, double c, double d, double e,
+                                            double& num, double& den) {
+    constexpr double C1 = 12.0 * WENO_EPS / 108.0, C2 = 13.0 / 3.0;
+    const double d1 = b - a, d2 = c - b, d3 = d - c, d4 = e - d;
+    const double t0 = d2 - d1, t1 = d3 - d2, t2 = d4 - d3;
+    const double u0 = 3.0 * d2 - d1, u1 = d2 + d3, u2 = 3.0 * d3 - d4;
+    const double b0 = C1 + (C2 * t0) * t0, b1 = C1 + (C2 * t1) * t1, b2 = C1 + (C2 * t2) * t2;
+    const double s0 = sq(b0 + u0 * u0), s1 = sq(b1 + u1 * u1), s2 = sq(b2 + u2 * u2);
+    const double w0 = s1 * s2, w1 = 6.0 * (s0 * s2), w2 = 3.0 * (s0 * s1);
+    const double r0 = 2.0 * u0 - d2, r1 = u1 + d3, r2 = d3 + u2;
+    num = w0 * r0 + (w1 * r1 + w2 * r2);
+    den = w0 + (w1 + w2);
+}
+
+// Numerical flux at an interface: WENO5 of F+ from p0..p4 plus WENO5 of F- from m0..m4
+// (its stencil mirrored). The detailed model takes both over one denominator.
+template <int M>
+__device__ __forceinline__ double weno5_flux(double p0, double p1, double p2, double p3, double p4,
+                                             double& m0, double m1, double m2, double m3, double m4) {
+    if constexpr (M == DETAILED) {
+        double np, dp, nm, dm;
+        weno5_parts(p0, p1, p2, p3, p4, np, dp);
+        after(dp, m0);
+        weno5_parts(m0, m1, m2, m3, m4, nm, dm);
+        const double q = quotient(np * dm + nm * dp, dp * dm);
+        return 6.0 * (p2 + m2) + q;
+    } else {
+        double h = weno5(p0, p1, p2, p3, p4);
+        after(h, m0);
+        return h + weno5(m0, m1, m2, m3, m4);
+    }
+}
+
+template <int M>
+__device__ __forceinline__ double weno5_pair(const double (&P)[5], double (&N)[5]) {
+    return weno5_flux<M>(P[0], P[1], P[2], P[3], P[4], N[0], N[1], N[2], N[3], N[4]);
+}
+
+// R consecutive interfaces from LDS strips of stride STR: F+ from p[k .. k+4], F- from
+// n[k+4 .. k]. Neighbouring stencils share their differences, second differences and their
+// squares. The strips are read as the run advances and the interfaces kept in order, so
+// that one interface's working set is live at a time (all R at once took 60 more registers).
+template <int M, int R, int STR>
+__device__ __forceinline__ void weno5_runs(const double* p, const double* n, double (&h)[R]) {
+    double P[R + 4], N[R + 4];
+#pragma unroll
+    for (int k = 0; k < 5; ++k) {
+        P[k] = p[k * STR];
+        N[k] = n[k * STR];
+    }
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+        if (k + 1 < R) {
+            P[k + 5] = p[(k + 5) * STR];
+            N[k + 5] = n[(k + 5) * STR];
+        }
+        h[k] = weno5_flux<M>(P[k], P[k + 1], P[k + 2], P[k + 3], P[k + 4],
+                             N[k + 4], N[k + 3], N[k + 2], N[k + 1], N[k]);
+        if (k + 1 < R) after(h[k], P[k + 5]);
+    }
 }
 
 __device__ __forceinline__ double rk_combine(int stage, double u0, double us, double L, double dt) {
@@ -369,7 +523,7 @@ __device__ __forceinline__ double cfl_bound(const StageArgs& a, CDom& D, int lev
 // This step's dt per domain (from buffer 0's CFL slots) into a.dt and the dt log.
 __device__ void record_dt(const StageArgs& a) {
     const int step = *a.step;
-    for (int d = threadIdx.x; d < a.ndom; d += WG) {
+    for (int d = threadIdx.x; d < a.ndom; d += (int)blockDim.x) {
         const double dt = step_dt(a, d, 0);
         a.dt[d] = dt;
         if (a.dt_log && step < a.dt_log_cap) a.dt_log[(size_t)step * a.ndom + d] = dt;
@@ -379,14 +533,14 @@ __device__ void record_dt(const StageArgs& a) {
 __device__ void stage_bookkeeping(const StageArgs& a, int owner_launch) {
     const int s = a.stage;
     const int bclear = (s + 1) % 3;
-    for (int q = threadIdx.x; q < a.red.stride; q += WG) a.red.buf[slot_word(a.red.stride, bclear, q)] = 0ull;
+    for (int q = threadIdx.x; q < a.red.stride; q += (int)blockDim.x) a.red.buf[slot_word(a.red.stride, bclear, q)] = 0ull;
     if (a.cross) owner_launch = a.xfirst;
     if (!owner_launch) return;
     if (s == 1 && !a.strang) record_dt(a);   // under Strang splitting the first chemistry launch does
 }
 
 __device__ void step_finish(const StageArgs& a) {
-    for (int d = threadIdx.x; d < a.ndom; d += WG) a.t[d] = a.t[d] + a.dt[d];
+    for (int d = threadIdx.x; d < a.ndom; d += (int)blockDim.x) a.t[d] = a.t[d] + a.dt[d];
     if (threadIdx.x == 0) *a.step = *a.step + 1;
 }
 

@@ -4,20 +4,29 @@
 //
 // One RK stage is one launch over a list of tiles (a tile is up to 16x16,
 // 32x8 or 64x4 cells of one block, or 256 cells of a one-dimensional block),
-// one 256-thread workgroup per tile. Per tile:
+// one workgroup of four wavefronts per tile. Per tile:
 //   phase 0  every cell of the tile plus 3 halo layers (cross-shaped; corners
 //            are not needed by the dimension-by-dimension sweeps) is fetched
 //            from its source -- the same block, a neighbouring block, the
 //            coarser level for coarse-fine ring cells, or a boundary rule --
-//            and its primitives are kept in registers;
-//   phase 1  per conserved component: Lax-Friedrichs split fluxes F+/F- and
-//            G+/G- (Eq. 4.11) go to LDS, WENO5 interface fluxes (Sec. 4.2)
-//            are reconstructed from LDS, and each owned cell forms the
-//            conservative difference (Eq. 4.10) and its Shu-Osher RK stage;
+//            and its velocities and pressure go to LDS;
+//   phase 1  each wavefront takes whole conserved components and, without any
+//            workgroup barrier, re-reads the component (L1/L2), forms the
+//            Lax-Friedrichs split fluxes F+/F- and then G+/G- (Eq. 4.11) in an
+//            LDS buffer of its own, reconstructs runs of four consecutive WENO5
+//            interfaces per lane (Sec. 4.2), and forms the conservative
+//            difference (Eq. 4.10) and the Shu-Osher RK stage of four cells a lane;
 //   phase 2  T of the new state (Newton warm-started from the previous stage
 //            for the NASA-7 model, Sec. 4.2), status checks, and the maxima of
 //            |u|+c, |v|+c and the CFL bound for the next stage, reduced per
-//            wavefront and published with one 64-bit atomic max per workgroup.
+//            workgroup and published with one 64-bit atomic max each.
+// Bound: FP64 VALU issue and the latency between the phases. Runs of four share the
+// differences and smoothness terms of neighbouring stencils (62 FP64 instructions per
+// interface of the 9-species model for 113 when every interface stood alone), and waves
+// that meet at two barriers per tile instead of twelve keep three workgroups per CU
+// apart in phase. 9 species, 1.92 M cells in 661 blocks: 0.305 -> 0.250 ms per stage,
+// 4,225 -> 3,240 VALU instructions per 64 cells; one-step, 131 k cells: 19.1 -> 16.6 us.
+// Four workgroups per CU (128 registers) spilled and were slower (0.29 ms).
 // Nothing here is a dense contraction, so there is no MFMA: the work is FP64
 // VALU arithmetic on values staged through LDS.
 #pragma once
@@ -27,53 +36,68 @@
 namespace janc {
 
 // ------------------------------------------------------------------ the stage tile
-// Conserved components reconstructed per pass between one pair of barriers: their
-// split fluxes go to separate LDS sets, so each thread has STAGE_CPB independent
-// WENO5 chains between the barriers and a stage has 2 ceil(NU / STAGE_CPB) barriers.
-#ifndef STAGE_CPB
-#define STAGE_CPB 2
-#endif
-// Points of a tile: the TX x TY owned positions first (point tid is thread tid's
-// own cell), then the x halo (3 columns each side of every row) and, for 2-D
-// tiles, the y halo (3 rows below and above every column).
+// A tile of TX x TY cells is swept by waves that each take whole conserved components
+// (wave w: components w, w + W, ..). A lane reconstructs runs of R = TX TY / 64
+// consecutive interfaces, along x in one pass and along y in the next, so that
+// neighbouring stencils share their differences and smoothness terms in registers.
+// Points of a tile: the owned cells first (point 64 q + l is cell q of lane l's y run, or
+// cell 64 q + l of a 1-D tile), then the x halo (3 columns each side of every row) and,
+// for 2-D tiles, the y halo (3 rows below and above every column).
 template <int TX, int TY>
 struct Geom {
     static constexpr bool TWO = TY > 1;
-    static constexpr int NC = TX * TY;
+    static constexpr int NC = TX * TY, R = NC / 64;
     static constexpr int NHX = 6 * TY, NHY = TWO ? 6 * TX : 0;
-    static constexpr int NP = NC + NHX + NHY, NPT = (NP + WG - 1) / WG;
-    static constexpr int PW = TX + 6;
-    static constexpr int NXS = PW * TY;                 // x split fluxes, row-major, 3 halo columns
-    static constexpr int NYS = TWO ? TX * (TY + 6) : 0; // y split fluxes, 3 halo rows
-    static constexpr int NIX = (TX + 1) * TY;           // x interfaces
-    static constexpr int NIY = TWO ? TX * (TY + 1) : 0; // y interfaces
+    static constexpr int NP = NC + NHX + NHY;
+    static constexpr int NPL = (NP + 63) / 64, NPP = 64 * NPL;   // points per lane of a wave
+    // split fluxes of one component in a wave's LDS buffer. x pass: rows of PX doubles, F+ of
+    // cell i at i + 3 and F- at i + 2 (a run's stencils of both start 16-byte aligned; the
+    // slots that this shift leaves unused take the F- of the first halo column). y pass: rows
+    // of PY doubles (16-wide tiles are padded so that the four y runs of a column fall on
+    // different banks). Then the numerical fluxes: x rows of HX, and the lowest y interface
+    // of every run plus the top row.
+    static constexpr int PX = TX + 6, PY = TX + (TX == 16 ? 2 : 0), HX = TX + 4;
+    static constexpr int NX = PX * TY, NY = TWO ? PY * (TY + 6) : 0, NH = HX * TY;
+    static constexpr int XR = TX / R;                 // x runs per row
     static constexpr int NEXT = TY + (TWO ? TX : 0);  // right column / top row interfaces
-    // LDS doubles of one set: F+/F- and G+/G-, then the numerical fluxes (sum of the
-    // two one-sided reconstructions) at the x and y interfaces; one set per component
-    // of a pass, then scratch
-    static constexpr int SET = 2 * NXS + 2 * NYS + NIX + NIY;
-    static constexpr int NSET = STAGE_CPB;
-    static constexpr int LDS = NSET * SET + 16;
-    static constexpr int oFPX = 0, oFMX = NXS, oFPY = 2 * NXS, oFMY = 2 * NXS + NYS;
-    static constexpr int oHX = 2 * NXS + 2 * NYS, oHY = oHX + NIX;
+    static constexpr int NHT = NH + (TWO ? (TY / R + 1) * TX : 0);
+    static constexpr int BUF0 = 2 * (NX > NY ? NX : NY);
+    static constexpr int BUF = BUF0 > NHT ? BUF0 : NHT;
+    static_assert(BUF % 2 == 0 && NX % 2 == 0, "16-byte alignment");
+    static_assert(NC % 64 == 0 && (R == 1 || R == 2 || R == 4), "tile shape");
 
     // tile-local position (li, lj) of point p
     __device__ static void point(int p, int& li, int& lj) {
         if (p < NC) {
-            lj = p / TX;
-            li = p - lj * TX;
+            const unsigned q = (unsigned)p >> 6, l = (unsigned)p & 63u;
+            li = TWO ? l % TX : p;
+            lj = TWO ? (l / TX) * R + q : 0;
         } else if (p < NC + NHX) {
-            const int h = p - NC, side = h / (3 * TY), r = h - side * 3 * TY;
-            lj = r / 3;
+            const int h = p - NC, side = h >= 3 * TY, r = h - side * 3 * TY;
+            lj = (r * 171) >> 9;   // r / 3 for r < 256
             li = side ? TX + (r - lj * 3) : (r - lj * 3) - 3;
         } else {
-            const int h = p - NC - NHX, side = h / (3 * TX), r = h - side * 3 * TX;
-            const int row = r / TX;
+            const int h = p - NC - NHX, side = h >= 3 * TX, r = h - side * 3 * TX;
+            const int row = (unsigned)r / TX;
             li = r - row * TX;
             lj = side ? TY + row : row - 3;
         }
     }
 };
+
+// Four waves sweep a 256-cell tile, one component each per round. One or two components
+// left over after whole rounds are swept by all four waves together, an interface of every
+// run each (a round of their own would leave three or two waves idle; workgroups of five
+// waves left the two of each CU that fit resident, half as many waves as four of four).
+constexpr int STAGE_W = 4;
+constexpr int stage_left(int nu) { return nu % STAGE_W <= 2 ? nu % STAGE_W : 0; }
+
+// LDS doubles of a stage workgroup: u, v, p (detailed model: times SPLIT_SCALE), source (32
+// bits) and flags (8 bits) of every point, one split-flux buffer per wave.
+template <int TX, int TY>
+constexpr int stage_lds() {
+    return 3 * Geom<TX, TY>::NPP + (5 * Geom<TX, TY>::NPP + 7) / 8 + STAGE_W * Geom<TX, TY>::BUF;
+}
 
 // Point p of a tile of tw x th valid cells: its tile-local position and whether the x
 // and the y sweep read it (the halo is cross-shaped).
@@ -90,249 +114,462 @@ __device__ __forceinline__ bool own_source(const DevBlock& B, int bi, int bj) {
     return bi >= 0 && bi < B.nx && bj >= 0 && bj < B.ny && !ring_at(B, bi, bj);
 }
 
-template <int M, int NU, int TX, int TY>
-__device__ void stage_tile(const StageArgs& a, const int ti, const Tile tile, double* smem) {
-    using G = Geom<TX, TY>;
-    static_assert(TX * TY == WG, "one owned cell per thread");
-    // set k at smem + k * SET: F+ / F- of x (fpx, fmx) and y (fpy, fmy), the WENO5 of
-    // F+ and F- at x interfaces (hxp, hxm) and y interfaces (hyp, hym)
-    double* scratch = smem + G::NSET * G::SET;
+// Flags of a point besides resolve()'s: its source is a row of the Dirichlet table; it is a
+// solved cell of the tile. Halo table word of a point that no sweep reads.
+constexpr unsigned PT_DIR = 8u, PT_OWN = 16u;
+constexpr int HALO_NONE = (int)0x80000000;
+template <bool WIDE> struct FlagWord { using type = unsigned; };
+template <> struct FlagWord<true> { using type = unsigned long long; };
 
+// Source (pool cell, or -(1 + Dirichlet row)) and flags of point p of a tile; false if no
+// sweep reads it.
+template <int TX, int TY>
+__device__ __forceinline__ bool point_source(const StageArgs& a, const DevBlock& B, CDom& D, const Tile& tile, int p,
+                                             int tw, int th, long long& s, unsigned& fl) {
+    int li, lj;
+    bool nx, ny;
+    point_needs<TX, TY>(p, tw, th, li, lj, nx, ny);
+    if (!(nx || ny)) return false;
+    const int bi = tile.x0 + li, bj = tile.y0 + lj;
+    if (own_source(B, bi, bj)) s = B.offset + (long long)bj * B.nx + bi;
+    else s = resolve(a, D, B.level, B.i0 + bi, B.j0 + bj, fl);
+    return true;
+}
+
+// Split fluxes F+- = (F +- alpha u) / 2 (Eq. 4.11) of a conserved value u, F = ue v + add,
+// at the scale they are kept in. Detailed model: v, alpha and add come scaled.
+template <int M>
+__device__ __forceinline__ void split_flux(double u, double v, double al, double add, double& Fp, double& Fm,
+                                           double ue) {
+    if constexpr (M == DETAILED) {
+        const double F = u * v + add, t = u * al;
+        Fp = F + t;
+        Fm = F - t;
+    } else {
+        double F = ue * v;
+        F += add;
+        Fp = SPLIT_SCALE<M> * (F + al * u);
+        Fm = SPLIT_SCALE<M> * (F - al * u);
+    }
+}
+
+// LDS accesses of one wave are executed in order; this keeps the compiler from moving them
+// across the point where lanes read what other lanes of their wave wrote.
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+template <int M, int NU, int TX, int TY>
+__device__ __forceinline__ void stage_tile(const StageArgs& a, const int ti, const Tile tile, double* smem) {
+    using G = Geom<TX, TY>;
+    constexpr int R = G::R, NPL = G::NPL, NPP = G::NPP, W = STAGE_W;
+    constexpr int LEFT = stage_left(NU), NR = NU - LEFT;   // components of whole rounds
+    static_assert(R == W && 2 * LEFT <= W, "left-over components: one interface of a run per wave, two buffers each");
+    constexpr bool DET = M == DETAILED;
+    constexpr double scale = DET ? SPLIT_SCALE<M> : 1.0;
+    double* pu = smem;                 // u, v, p of every point, times scale
+    double* pv = pu + NPP;
+    double* pp = pv + NPP;
+    double* bufs = pp + NPP;
+    unsigned* psrc = (unsigned*)(bufs + W * G::BUF);
+    unsigned char* pfl = (unsigned char*)(psrc + NPP);
+
+    // ---------------- phase 0: source and primitives of every point of the tile and its halo
+    // Everything a thread loads is on its way before it waits: the table words of its NT
+    // points first (they need the tile number alone), then all fields of the points.
+    constexpr int NT = (NPP + 64 * W - 1) / (64 * W);
     const int tid = threadIdx.x;
-    const DevBlock B = a.blk[tile.block];
+    int hv[NT];
+#pragma unroll
+    for (int k = 0; k < NT; ++k) {
+        const int p = tid + 64 * W * k;
+        hv[k] = (a.hsrc && p < G::NP) ? a.hsrc[(size_t)ti * a.hstride + p] : HALO_NONE;
+    }
+    const DevBlock B = cblock(a.blk, tile.block);
     CDom& D = cdom(a.dom, B.domain);
     const int lev = B.level;
     const int stage = a.stage;
     const int bin = (stage == 1 && a.strang) ? 3 : stage - 1, bout = stage % 3;
+    const int slot = D.slot0 + lev;
+    const int tw = min(TX, B.nx - tile.x0), th = min(TY, B.ny - tile.y0);
+    double ur[NT][NU], Tr[NT];
+    unsigned src[NT], pfl0[NT];
+#pragma unroll
+    for (int k = 0; k < NT; ++k) {
+        const int p = tid + 64 * W * k;
+        long long s = (long long)(hv[k] >> 3);
+        unsigned fl = (unsigned)(hv[k] & 7);
+        bool needed = hv[k] != HALO_NONE;
+        if (!a.hsrc) {
+            fl = 0u;
+            needed = p < G::NP && point_source<TX, TY>(a, B, D, tile, p, tw, th, s, fl);
+        }
+        // points that no sweep reads stand on the block's first cell; crossover: coarser
+        // levels are read at their current state
+        if (!needed) {
+            s = B.offset;
+            fl = 0u;
+        }
+        const bool base = a.cross && (fl & 4u);
+        src[k] = (unsigned)(s < 0 ? -s - 1 : s);
+        pfl0[k] = (base ? fl : (fl & 3u)) | (s < 0 ? PT_DIR : 0u);
+        if (k == 0) {   // a valid cell of the tile is solved unless it is a ring cell
+            int li, lj; // (a coarser source)
+            G::point(tid, li, lj);
+            if (needed && li < tw && lj < th && !(fl & 4u)) pfl0[k] |= PT_OWN;
+        }
+        const size_t c = s < 0 ? 0 : (size_t)s;
+        const double* U = (base ? a.U0 : a.Uin) + c;
+#pragma unroll
+        for (int f = 0; f < NU; ++f) ur[k][f] = U[(size_t)f * a.pool];
+        Tr[k] = (base ? a.Tbase : a.Tin)[c];
+    }
+#pragma unroll
+    for (int k = 0; k < NT; ++k)
+        if (pfl0[k] & PT_DIR) {
+            const double* r = a.dirU + (size_t)src[k] * (MAXF + 1);
+#pragma unroll
+            for (int f = 0; f < NU; ++f) ur[k][f] = r[f];
+            Tr[k] = r[MAXF];
+        }
     // crossover advance: dt_l = dt_0 / 2^l, dt_0 formed by the first launch of the step
-    const double dt = a.cross ? ldexp((a.xfirst && stage == 1) ? step_dt(a, B.domain, 0)
-                                                               : a.dt[B.domain], -lev)
-                              : (stage == 1) ? step_dt(a, B.domain, 0) : a.dt[B.domain];
+    const double dt = uniform(a.cross ? ldexp((a.xfirst && stage == 1) ? step_dt(a, B.domain, 0)
+                                                                       : a.dt[B.domain], -lev)
+                                      : (stage == 1) ? step_dt(a, B.domain, 0) : a.dt[B.domain]);
     if (!(dt > 0.0)) return;   // finished domain: state unchanged
     const double dxl = D.dx0 / (double)(1 << lev), dyl = D.dy0 / (double)(1 << lev);
-    const double idx = 1.0 / dxl, idy = 1.0 / dyl;
-    const int slot = D.slot0 + lev;
-    const double ax = slot_get(a.red, bin, 2 * slot);
-    const double ay = slot_get(a.red, bin, 2 * slot + 1);
-    const int tw = min(TX, B.nx - tile.x0), th = min(TY, B.ny - tile.y0);
-
-    // ---------------- phase 0: fetch the tile and its halo, primitives in registers
-    double ur[G::NPT][NU];
-    double vxr[G::NPT], vyr[G::NPT], pr[G::NPT];
-    bool needx[G::NPT], needy[G::NPT];
-    int xoff[G::NPT], yoff[G::NPT];
-    double Town = 0.0;
+    const double idx = uniform(1.0 / dxl), idy = uniform(1.0 / dyl);
+    const double ax = uniform(slot_get(a.red, bin, 2 * slot));
+    const double ay = uniform(slot_get(a.red, bin, 2 * slot + 1));
+    const double sax = uniform(scale * ax), say = uniform(scale * ay);
+    const double Town = Tr[0];   // T of the cell this thread solves in phase 2
+    double src_e = 0.0;          // its explicit source, one-step model (Sec. 4.3)
+    double uleft[LEFT + 1];      // its left-over components
 #pragma unroll
-    for (int q = 0; q < G::NPT; ++q) {
-        const int p = tid + q * WG;
-        needx[q] = needy[q] = false;
-        xoff[q] = yoff[q] = 0;
-        vxr[q] = vyr[q] = pr[q] = 0.0;
+    for (int k = 0; k < LEFT; ++k) uleft[k] = ur[0][NR + k];
 #pragma unroll
-        for (int f = 0; f < NU; ++f) ur[q][f] = 0.0;
-        // the table word is loaded for every point (one coalesced row per tile) ahead of
-        // the test that decides whether it is used
-        const int hv = (a.hsrc && p < G::NP) ? a.hsrc[(size_t)ti * a.hstride + p] : 0;
-        if (p < G::NP) {
+    for (int k = 0; k < NT; ++k) {
+        const int p = tid + 64 * W * k;
+        if (p >= NPP) continue;
+        if (pfl0[k] & 1u) ur[k][1] = -ur[k][1];
+        if (pfl0[k] & 2u) ur[k][2] = -ur[k][2];
+        double vx, vy, pr;
+        halo_prims<M, NU>(ur[k], Tr[k], D, cmech(a.mech), vx, vy, pr);
+#pragma unroll
+        for (int j = 0; j < LEFT; ++j) {   // species rows: no pressure term
+            double* X = bufs + 2 * j * G::BUF;
+            double* Y = X + G::BUF;
+            const double uk = ur[k][NR + j];
             int li, lj;
-            point_needs<TX, TY>(p, tw, th, li, lj, needx[q], needy[q]);
-            xoff[q] = lj * G::PW + li + 3;
-            yoff[q] = (lj + 3) * TX + li;
-            if (needx[q] || needy[q]) {
-                const int bi = tile.x0 + li, bj = tile.y0 + lj;
-                long long src;
-                unsigned fl = 0u;
-                if (own_source(B, bi, bj)) {
-                    src = B.offset + (long long)bj * B.nx + bi;
-                } else if (a.hsrc) {
-                    src = (long long)(hv >> 3);
-                    fl = (unsigned)(hv & 7);
-                } else {
-                    src = resolve(a, D, lev, B.i0 + bi, B.j0 + bj, fl);
-                }
-                double T;
-                // crossover: coarser levels are read at their current state
-                const bool base = a.cross && (fl & 4u);
-                fetch<NU>(a, src, fl, base ? a.U0 : a.Uin, base ? a.Tbase : a.Tin, ur[q], T);
-                halo_prims<M, NU>(ur[q], T, D, cmech(a.mech), vxr[q], vyr[q], pr[q]);
-                if (q == 0) Town = T;
+            G::point(p, li, lj);
+            if (p < G::NC + G::NHX) {
+                const int o = lj * G::PX + li + 3;
+                split_flux<M>(uk, scale * vx, sax, 0.0, X[o], X[G::NX - 1 + o], uk);
+            }
+            if (G::TWO && (p < G::NC || (p >= G::NC + G::NHX && p < G::NP))) {
+                const int o = (lj + 3) * G::PY + li;
+                split_flux<M>(uk, scale * vy, say, 0.0, Y[o], Y[G::NY + o], uk);
             }
         }
-    }
-
-    // owned cell: point tid, held in ur[0]
-    const int oli = tid % TX, olj = tid / TX;
-    const int obi = tile.x0 + oli, obj = tile.y0 + olj;
-    const bool own = (oli < tw) && (olj < th) && !ring_at(B, obi, obj);
-    const long long oc = B.offset + (long long)obj * B.nx + obi;
-    double src_e = 0.0;   // explicit source of the one-step model (Sec. 4.3)
-    if constexpr (M == ONESTEP) {
-        if (own) {
-            const double Tc = pr[0] / (ur[0][0] * D.R);
-            src_e = -D.k * ur[0][4] * exp(-D.Ea / Tc);
+        if constexpr (M == ONESTEP) {
+            if (k == 0) {
+                const double Tc = pr / (ur[k][0] * D.R);
+                src_e = -D.k * ur[k][4] * exp(-D.Ea / Tc);
+            }
         }
+        pu[p] = scale * vx;
+        pv[p] = scale * vy;
+        pp[p] = scale * pr;
+        psrc[p] = src[k];
+        pfl[p] = (unsigned char)pfl0[k];
     }
-    double unew[NU];
-
-    // reconstruction tasks of this thread (see phase 1)
-    const bool vxi = (olj < th) && (oli <= tw);
-    const bool vyi = G::TWO && (oli < tw) && (olj <= th);
-    const int bxi = olj * G::PW + oli, byi = olj * TX + oli;
-    const int rxi = olj * (TX + 1) + oli, ryi = olj * TX + oli;
-    bool ext_ok = false;
-    int ext_str = 1, ext_p = 0, ext_m = 0, ext_out = 0;   // offsets within a set
-    if (tid < G::NEXT) {
-        const int e = tid;
-        if (e < TY) {              // x interface TX of row e
-            ext_ok = e < th && tw == TX;
-            const int o = e * G::PW + TX;
-            ext_p = G::oFPX + o;
-            ext_m = G::oFMX + o;
-            ext_str = 1;
-            ext_out = G::oHX + e * (TX + 1) + TX;
-        } else {                   // y interface TY of column e - TY
-            const int col = e - TY;
-            ext_ok = col < tw && th == TY;
-            const int o = TY * TX + col;
-            ext_p = G::oFPY + o;
-            ext_m = G::oFMY + o;
-            ext_str = TX;
-            ext_out = G::oHY + TY * TX + col;
-        }
-    }
+    __syncthreads();
 
     // ---------------- phase 1: per component split fluxes, WENO5, RK update
-    // U^(0) of the owned cell (stages 2 and 3) is loaded PF components ahead of
-    // its use, so that its memory latency overlaps the reconstructions between.
-    constexpr int PF = 3;
-    const bool ld0 = own && stage != 1;
-    double u0q[PF];
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
+    double* S = bufs + w * G::BUF;
+    double* SM = S + G::NX - 1;          // F- of the x pass: cell i at PX row + i + 2
+    double* SY = S + G::NY;              // F- of the y pass
+    double* SH = S + G::NH;              // lowest y fluxes of the runs
+    // sources and flags (4 bits a point) of the lane's points
+    using Flags = typename FlagWord<(NPL > 8)>::type;
+    unsigned sp[NPL];
+    Flags pf = 0;
+    unsigned own = 0u;                    // bit q: cell q of this lane is solved
+    int hoff[NPL];                        // LDS offset of a halo point in its pass
 #pragma unroll
-    for (int k = 0; k < PF; ++k) u0q[k] = (ld0 && k < NU) ? a.U0[(size_t)k * a.pool + oc] : 0.0;
-    // split fluxes of component f (Eq. 4.11) into set S
-    auto flux = [&](int f, double* S) {
-#pragma unroll
-        for (int q = 0; q < G::NPT; ++q) {
-            const double uf = ur[q][f];
-            if (needx[q]) {
-                double F = uf * vxr[q];
-                if (f == 1) F += pr[q];
-                if (f == 3) F = (uf + pr[q]) * vxr[q];
-                S[G::oFPX + xoff[q]] = 0.5 * (F + ax * uf);
-                S[G::oFMX + xoff[q]] = 0.5 * (F - ax * uf);
-            }
-            if constexpr (G::TWO) {
-                if (needy[q]) {
-                    double Gf = uf * vyr[q];
-                    if (f == 2) Gf += pr[q];
-                    if (f == 3) Gf = (uf + pr[q]) * vyr[q];
-                    S[G::oFPY + yoff[q]] = 0.5 * (Gf + ay * uf);
-                    S[G::oFMY + yoff[q]] = 0.5 * (Gf - ay * uf);
-                }
-            }
-        }
-    };
-    // WENO5 reconstructions from set S into set S: each thread takes the left x
-    // interface and the lower y interface of its own position (both one-sided values,
-    // summed: the numerical flux), at fixed LDS offsets; the right column and top row
-    // of interfaces are the extra tasks of the first threads. F- reads its stencil
-    // mirrored.
-    auto recon = [&](double* S) {
-        if (vxi) {
-            const double* P = S + G::oFPX + bxi;
-            const double* Mn = S + G::oFMX + bxi;
-            S[G::oHX + rxi] = weno5(P[0], P[1], P[2], P[3], P[4]) +
-                              weno5(Mn[5], Mn[4], Mn[3], Mn[2], Mn[1]);
-        }
-        if constexpr (G::TWO) {
-            if (vyi) {
-                const double* P = S + G::oFPY + byi;
-                const double* Mn = S + G::oFMY + byi;
-                S[G::oHY + ryi] = weno5(P[0], P[TX], P[2 * TX], P[3 * TX], P[4 * TX]) +
-                                  weno5(Mn[5 * TX], Mn[4 * TX], Mn[3 * TX], Mn[2 * TX], Mn[TX]);
-            }
-        }
-        if (ext_ok) {
-            const double* P = S + ext_p;
-            const double* Mn = S + ext_m;
-            const int k = ext_str;
-            S[ext_out] = weno5(P[0], P[k], P[2 * k], P[3 * k], P[4 * k]) +
-                         weno5(Mn[5 * k], Mn[4 * k], Mn[3 * k], Mn[2 * k], Mn[k]);
-        }
-    };
-    // flux difference (Eq. 4.10), source and RK stage of component f from set S
-    auto update = [&](int f, const double* S, double u0) {
-        if (own) {
-            const double* hx = S + G::oHX;
-            const int rx = olj * (TX + 1) + oli;
-            double L = -(hx[rx + 1] - hx[rx]) * idx;
-            if constexpr (G::TWO) {
-                const double* hy = S + G::oHY;
-                const int ry = olj * TX + oli;
-                L -= (hy[ry + TX] - hy[ry]) * idy;
-            }
-            if constexpr (M == ONESTEP) {
-                if (f == 4) L += src_e;
-            }
-            const double un = rk_combine(stage, u0, ur[0][f], L, dt);
-            a.Uout[(size_t)f * a.pool + oc] = un;
-            unew[f] = un;
-        }
-    };
-    constexpr int CPB = G::NSET;
-#pragma unroll
-    for (int f0 = 0; f0 < NU; f0 += CPB) {
-#pragma unroll
-        for (int k = 0; k < CPB; ++k)
-            if (f0 + k < NU) flux(f0 + k, smem + k * G::SET);
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < CPB; ++k)
-            if (f0 + k < NU) recon(smem + k * G::SET);
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < CPB; ++k) {
-            const int f = f0 + k;
-            if (f < NU) {
-                const double u0 = (stage == 1) ? ur[0][f] : u0q[f % PF];
-                if (f + PF < NU) u0q[f % PF] = ld0 ? a.U0[(size_t)(f + PF) * a.pool + oc] : 0.0;
-                update(f, smem + k * G::SET, u0);
-            }
+    for (int q = 0; q < NPL; ++q) {
+        sp[q] = psrc[64 * q + l];
+        const unsigned fl = pfl[64 * q + l];
+        pf |= (Flags)(fl & 15u) << (4 * q);
+        if (q < R) own |= (fl & PT_OWN) ? 1u << q : 0u;
+        hoff[q] = 0;
+        if (q >= R) {
+            int li, lj;
+            G::point(64 * q + l, li, lj);
+            hoff[q] = (64 * q + l < G::NC + G::NHX) ? lj * G::PX + li + 3 : (lj + 3) * G::PY + li;
         }
     }
+    const bool special = __any((pf & (Flags)0xccccccccccccccccull) != 0);
+    const int oli = G::TWO ? l % TX : l, olj = G::TWO ? (l / TX) * R : 0;
+    const int xbase = (l / G::XR) * G::PX + (l % G::XR) * R;
+    const int ybase = G::TWO ? olj * G::PY + oli : 0;
+    // RK stage (Shu-Osher): ca U^n + cb (U + dt L)
+    const double ca = (stage == 1) ? 0.0 : (stage == 2) ? 0.75 : 1.0 / 3.0;
+    const double cb = (stage == 1) ? 1.0 : (stage == 2) ? 0.25 : 2.0 / 3.0;
+    if constexpr (LEFT > 0) {   // components left over: wave w takes interface w of every run
+        double hx[LEFT], hy[LEFT], he[LEFT];
+#pragma unroll
+        for (int k = 0; k < LEFT; ++k) {
+            const double* X = bufs + 2 * k * G::BUF;
+            const double* Y = X + G::BUF;
+            double h1[1];
+            weno5_runs<M, 1, 1>(X + xbase + w, X + G::NX + xbase + w, h1);
+            hx[k] = h1[0];
+            hy[k] = he[k] = 0.0;
+            if constexpr (G::TWO) {
+                weno5_runs<M, 1, G::PY>(Y + ybase + w * G::PY, Y + G::NY + ybase + (w + 1) * G::PY, h1);
+                hy[k] = h1[0];
+            }
+            if (tid < G::NEXT) {   // right column, top row
+                if (tid < TY) weno5_runs<M, 1, 1>(X + tid * G::PX + TX, X + G::NX + tid * G::PX + TX, h1);
+                else weno5_runs<M, 1, G::PY>(Y + TY * G::PY + tid - TY, Y + G::NY + (TY + 1) * G::PY + tid - TY, h1);
+                he[k] = h1[0];
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < LEFT; ++k) {
+            double* X = bufs + 2 * k * G::BUF;
+            double* Y = X + G::BUF;
+            X[(l / G::XR) * G::HX + (l % G::XR) * R + w] = hx[k];
+            if (G::TWO) Y[(olj + w) * TX + oli] = hy[k];
+            if (tid < TY) X[tid * G::HX + TX] = he[k];
+            else if (tid < G::NEXT) Y[TY * TX + tid - TY] = he[k];
+        }
+        __syncthreads();
+        if ((own >> w) & 1u) {
+            const unsigned c = psrc[tid];
+#pragma unroll
+            for (int k = 0; k < LEFT; ++k) {
+                const double* X = bufs + 2 * k * G::BUF;
+                const double* Y = X + G::BUF;
+                const int o = G::TWO ? (olj + w) * G::HX + oli : tid;
+                double L = -(X[o + 1] - X[o]) * idx;
+                if constexpr (G::TWO) L -= (Y[(olj + w + 1) * TX + oli] - Y[(olj + w) * TX + oli]) * idy;
+                if constexpr (M == ONESTEP) L += src_e;
+                const double u0 = (stage != 1) ? a.U0[(size_t)(NR + k) * a.pool + c] : 0.0;
+                a.Uout[(size_t)(NR + k) * a.pool + c] = ca * u0 + cb * (uleft[k] + dt * L);
+            }
+        }
+        __syncthreads();
+    }
+    // component f of the lane's points
+    auto load = [&](int f, double (&u)[NPL]) {
+        const double* Uf = a.Uin + (size_t)f * a.pool;
+        if (!special) {
+#pragma unroll
+            for (int q = 0; q < NPL; ++q) u[q] = Uf[sp[q]];
+        } else {
+            const double* U0f = a.U0 + (size_t)f * a.pool;
+#pragma unroll
+            for (int q = 0; q < NPL; ++q) {
+                const unsigned fl = (unsigned)(pf >> (4 * q)) & 15u;
+                const double* F = (fl & PT_DIR) ? a.dirU + f : (fl & 4u) ? U0f : Uf;
+                u[q] = F[(fl & PT_DIR) ? sp[q] * (unsigned)(MAXF + 1) : sp[q]];
+            }
+        }
+    };
+    double u[NPL], un[NPL];   // this component and, on its way, the wave's next one
+    load(w, un);
+    for (int f = w; f < NR; f += W) {
+        // opaque in every pass: values derived from these are formed where they are used
+        // (hoisted out of the loop they took 70 registers)
+        asm volatile("" : "+v"(pf), "+v"(own));
+#pragma unroll
+        for (int q = 0; q < NPL; ++q) asm volatile("" : "+v"(sp[q]), "+v"(hoff[q]));
+        const double* U0f = a.U0 + (size_t)f * a.pool;
+        double u0[R];
+#pragma unroll
+        for (int q = 0; q < NPL; ++q) u[q] = un[q];
+#pragma unroll
+        for (int q = 0; q < R; ++q) u0[q] = 0.0;
+        if (stage != 1) {
+#pragma unroll
+            for (int q = 0; q < R; ++q) u0[q] = U0f[((own >> q) & 1u) ? sp[q] : (unsigned)B.offset];
+        }
+        if (f == 1 || f == 2) {
+#pragma unroll
+            for (int q = 0; q < NPL; ++q) u[q] = ((unsigned)(pf >> (4 * q)) & (unsigned)f) ? -u[q] : u[q];
+        }
+        // split fluxes of point q along x or y; `plain`: neither the momentum along the sweep
+        // nor the energy, which carry the pressure
+        auto split = [&](int q, const double* pn, double al, bool plain, double& Fp, double& Fm) {
+            const double vn = pn[64 * q + l];
+            double F = 0.0, ue = u[q];   // pressure terms of the flux
+            if (!plain) {
+                const double p = pp[64 * q + l];
+                if constexpr (DET) {
+                    F = (f == 3) ? (p * vn) * (1.0 / scale) : p;
+                } else {
+                    ue += (f == 3) ? p : 0.0;
+                    F = (f == 3) ? 0.0 : p;
+                }
+            }
+            split_flux<M>(u[q], vn, al, F, Fp, Fm, ue);
+        };
+        auto xfluxes = [&](bool plain) {
+#pragma unroll
+            for (int q = 0; q < NPL; ++q) {
+                if (64 * q >= G::NC + G::NHX) continue;
+                const int o = (q < R) ? (G::TWO ? (olj + q) * G::PX + oli + 3 : 64 * q + l + 3) : hoff[q];
+                if (64 * q + 64 <= G::NC + G::NHX || 64 * q + l < G::NC + G::NHX) {
+                    double Fp, Fm;
+                    split(q, pu, sax, plain, Fp, Fm);
+                    S[o] = Fp;
+                    SM[o] = Fm;
+                }
+            }
+        };
+        auto yfluxes = [&](bool plain) {
+#pragma unroll
+            for (int q = 0; q < NPL; ++q) {
+                if (q >= R && 64 * q + 64 <= G::NC + G::NHX) continue;
+                const int o = (q < R) ? (olj + q + 3) * G::PY + oli : hoff[q];
+                if (q < R || ((64 * q >= G::NC + G::NHX || 64 * q + l >= G::NC + G::NHX) &&
+                              (64 * q + 64 <= G::NP || 64 * q + l < G::NP))) {
+                    double Fp, Fm;
+                    split(q, pv, say, plain, Fp, Fm);
+                    S[o] = Fp;
+                    SY[o] = Fm;
+                }
+            }
+        };
+        double eP[5], eM[5];   // stencils of the right column / top row interface of this lane
+#pragma unroll
+        for (int k = 0; k < 5; ++k) eP[k] = eM[k] = 0.0;
+        // x pass
+        double hx[R];
+        if (f == 1 || f == 3) xfluxes(false);
+        else xfluxes(true);
+        if (f + W < NR) load(f + W, un);
+        wave_sync();
+        {
+            if (l < TY) {
+                const int o = l * G::PX + TX;
+#pragma unroll
+                for (int k = 0; k < 5; ++k) {
+                    eP[k] = S[o + k];
+                    eM[k] = S[G::NX + o + 4 - k];
+                }
+            }
+            weno5_runs<M, R, 1>(S + xbase, S + G::NX + xbase, hx);
+        }
+        wave_sync();
+        // y pass
+        double hy[R + 1];
+        if constexpr (G::TWO) {
+            if (f == 2 || f == 3) yfluxes(false);
+            else yfluxes(true);
+            wave_sync();
+            double h[R];
+            const int e = l - (G::NEXT <= 64 ? TY : 0);   // top row, column e
+            if (e >= 0 && e < TX && G::NEXT <= 64) {
+                const int o = TY * G::PY + e;
+#pragma unroll
+                for (int k = 0; k < 5; ++k) {
+                    eP[k] = S[o + k * G::PY];
+                    eM[k] = SY[o + (5 - k) * G::PY];
+                }
+            }
+            double tP[5], tM[5];
+            if constexpr (G::NEXT > 64) {
+#pragma unroll
+                for (int k = 0; k < 5; ++k) {
+                    tP[k] = S[TY * G::PY + l + k * G::PY];
+                    tM[k] = SY[TY * G::PY + l + (5 - k) * G::PY];
+                }
+            }
+            weno5_runs<M, R, G::PY>(S + ybase, SY + G::PY + ybase, h);
+#pragma unroll
+            for (int k = 0; k < R; ++k) hy[k] = h[k];
+            wave_sync();
+            SH[(l / TX) * TX + oli] = h[0];
+            if constexpr (G::NEXT > 64) SH[(TY / R) * TX + l] = weno5_pair<M>(tP, tM);
+        }
+        // numerical fluxes to LDS, the right column and top row with them
+#pragma unroll
+        for (int k = 0; k < R; ++k) S[(l / G::XR) * G::HX + (l % G::XR) * R + k] = hx[k];
+        if (G::NEXT > 64 ? l < TY : l < G::NEXT) {
+            const double he = weno5_pair<M>(eP, eM);
+            if (l < TY) S[l * G::HX + TX] = he;
+            else SH[(TY / R) * TX + l - TY] = he;
+        }
+        wave_sync();
+        if constexpr (G::TWO) hy[R] = SH[(l / TX + 1) * TX + oli];
+        // flux difference (Eq. 4.10), source and RK stage
+        double L[R];
+#pragma unroll
+        for (int q = 0; q < R; ++q) {
+            const int o = G::TWO ? (olj + q) * G::HX + oli : 64 * q + l;
+            L[q] = -(S[o + 1] - S[o]) * idx;
+            if constexpr (G::TWO) L[q] -= (hy[q + 1] - hy[q]) * idy;
+        }
+        double* out = a.Uout + (size_t)f * a.pool;
+#pragma unroll
+        for (int q = 0; q < R; ++q) {
+            const double unew = ca * u0[q] + cb * (u[q] + dt * L[q]);
+            if ((own >> q) & 1u) out[sp[q]] = unew;
+        }
+        wave_sync();
+    }
+    __syncthreads();   // the new state of the tile is complete (in the caches)
 
     // ---------------- phase 2: T, checks, maxima for the next stage
     double sx = 0.0, sy = 0.0, sc = 0.0;
-    if (own) {
+    if ((own >> w) & 1u) {   // cell tid = 64 w + l
+        const long long oc = psrc[tid];
+        double unew[NU];
+#pragma unroll
+        for (int f = 0; f < NU; ++f) unew[f] = a.Uout[(size_t)f * a.pool + oc];
         double T, c, vx, vy;
         const unsigned st = owner_state<M, NU>(unew, Town, D, cmech(a.mech), T, c, vx, vy);
         a.Tout[oc] = T;
         if (st) atomicOr(a.status, st);
-        const bool skip = (stage == 3) && B.fine_child && (!a.cross || a.xskip_cov) &&
-                          covered_by_finer(a, D, lev, B.i0 + obi, B.j0 + obj);
+        bool skip = false;
+        if (stage == 3 && B.fine_child && (!a.cross || a.xskip_cov)) {
+            int li, lj;
+            G::point(tid, li, lj);
+            skip = covered_by_finer(a, D, lev, B.i0 + tile.x0 + li, B.j0 + tile.y0 + lj);
+        }
         if (a.reduce_out && !st && !skip) {
             sx = fabs(vx) + c;
             sy = fabs(vy) + c;
             sc = cfl_bound(a, D, lev, sx, sy, idx, idy);
         }
     }
-    if (a.reduce_out)
-        publish_max3(a.red, bout, 2 * slot, 2 * slot + 1, 2 * a.red.nunits + B.domain, sx, sy, sc,
-                     scratch);
+    if (a.reduce_out) {
+        bufs[tid] = sx;
+        bufs[256 + tid] = sy;
+        bufs[512 + tid] = sc;
+        __syncthreads();
+        publish_staged(a.red, bout, 2 * slot, 2 * slot + 1, 2 * a.red.nunits + B.domain, bufs);
+    }
 }
 
 #ifndef STAGE_WAVES
 #define STAGE_WAVES 1
 #endif
 template <int M, int NU, int TX, int TY, bool HAS1D, bool HAS2D>
-__global__ __launch_bounds__(WG, STAGE_WAVES) void stage_kernel(StageArgs a, int first_tile, int owner_launch) {
-    constexpr int L2 = Geom<TX, TY>::LDS, L1 = Geom<WG, 1>::LDS;
-    __shared__ double smem[(L2 > L1) ? L2 : L1];
+__global__ __launch_bounds__(64 * STAGE_W, STAGE_WAVES) void stage_kernel(StageArgs a, int first_tile, int owner_launch) {
+    constexpr int L2 = HAS2D ? stage_lds<TX, TY>() : 0, L1 = HAS1D ? stage_lds<256, 1>() : 0;
+    __shared__ __align__(16) double smem[(L2 > L1) ? L2 : L1];
     if (blockIdx.x == 0) stage_bookkeeping(a, owner_launch);
     const int ti = first_tile + (a.linear_sched ? (int)blockIdx.x : xcd_chunk(blockIdx.x, gridDim.x));
-    const Tile tile = a.tiles[ti];
+    const Tile tile = ctile(a.tiles, ti);
     if (HAS1D && tile.kind == 1) {
-        if constexpr (HAS1D) stage_tile<M, NU, WG, 1>(a, ti, tile, smem);
+        if constexpr (HAS1D) stage_tile<M, NU, 256, 1>(a, ti, tile, smem);
     } else {
         if constexpr (HAS2D) stage_tile<M, NU, TX, TY>(a, ti, tile, smem);
     }
@@ -343,27 +580,19 @@ __global__ __launch_bounds__(WG, STAGE_WAVES) void stage_kernel(StageArgs a, int
 }
 
 // ------------------------------------------------------------------ halo source table
-// Workgroup t fills row t of the table: for each point of tile t that a sweep reads and
-// that is not its own block's cell, 8 * resolve() + its flags (bit 0 / 1: mirrored x / y
-// momentum, bit 2: a coarser level); 0 elsewhere (never read).
+// Workgroup t fills row t of the table: for each point of tile t that a sweep reads,
+// 8 * source + flags (bit 0 / 1: mirrored x / y momentum, bit 2: a coarser level);
+// HALO_NONE elsewhere.
 template <int TX, int TY>
 __device__ void halo_table_tile(const StageArgs& a, int ti, const Tile& tile, int* row) {
-    using G = Geom<TX, TY>;
     const DevBlock B = a.blk[tile.block];
     CDom& D = cdom(a.dom, B.domain);
     const int tw = min(TX, B.nx - tile.x0), th = min(TY, B.ny - tile.y0);
-    for (int p = threadIdx.x; p < G::NP; p += WG) {
-        int li, lj;
-        bool nx, ny;
-        point_needs<TX, TY>(p, tw, th, li, lj, nx, ny);
-        int v = 0;
-        const int bi = tile.x0 + li, bj = tile.y0 + lj;
-        if ((nx || ny) && !own_source(B, bi, bj)) {
-            unsigned fl = 0u;
-            const long long src = resolve(a, D, B.level, B.i0 + bi, B.j0 + bj, fl);
-            v = (int)(src * 8 + (long long)fl);
-        }
-        row[p] = v;
+    for (int p = threadIdx.x; p < Geom<TX, TY>::NP; p += WG) {
+        long long s = 0;
+        unsigned fl = 0u;
+        const bool needed = point_source<TX, TY>(a, B, D, tile, p, tw, th, s, fl);
+        row[p] = needed ? (int)(s * 8 + (long long)fl) : HALO_NONE;
     }
 }
 
@@ -434,7 +663,7 @@ __global__ __launch_bounds__(WG) void init_kernel(StageArgs a) {
             sc = cfl_bound(a, D, lev, sx, sy, idx, idy);
         }
     }
-    publish_max3(a.red, 0, 2 * slot, 2 * slot + 1, 2 * a.red.nunits + B.domain, sx, sy, sc, scratch);
+    publish_max3<WG / 64>(a.red, 0, 2 * slot, 2 * slot + 1, 2 * a.red.nunits + B.domain, sx, sy, sc, scratch);
 }
 
 // (I - dt J) dU = dt w of the point-implicit step (Eq. 4.12-4.13) for the Jacobian J of
@@ -715,7 +944,7 @@ __device__ __forceinline__ void chem_body(const StageArgs& a, double* scratch, C
             sc = cfl_bound(a, D, lev, sx, sy, idx, idy);
         }
     }
-    publish_max3(a.red, (phase == 1) ? 3 : 0, 2 * slot, 2 * slot + 1, 2 * a.red.nunits + B.domain, sx,
+    publish_max3<WG / 64>(a.red, (phase == 1) ? 3 : 0, 2 * slot, 2 * slot + 1, 2 * a.red.nunits + B.domain, sx,
                  sy, sc, scratch);
 }
 
@@ -783,7 +1012,7 @@ __global__ __launch_bounds__(WG) void restrict_kernel(StageArgs a, const int* fi
             sc = fmax(sc, cfl_bound(a, D, lev - 1, fabs(vx) + c, fabs(vy) + c, idx, idy));
         }
     }
-    publish_max3(a.red, 0, 2 * cslot, 2 * cslot + 1, 2 * a.red.nunits + B.domain, sx, sy, sc,
+    publish_max3<WG / 64>(a.red, 0, 2 * cslot, 2 * cslot + 1, 2 * a.red.nunits + B.domain, sx, sy, sc,
                  scratch);
 }
 

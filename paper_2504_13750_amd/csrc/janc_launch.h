@@ -12,9 +12,9 @@ hipError_t launch_stage_m(int kind_mask, int tile_w, const StageArgs& a, int fir
     const bool h1 = kind_mask & 2, h2 = kind_mask & 1;
 #define JANC_STAGE(TXv, TYv)                                                                      \
     do {                                                                                          \
-        if (h1 && h2) stage_kernel<M, NU, TXv, TYv, true, true><<<n, WG, 0, s>>>(a, first, owner);   \
-        else if (h1) stage_kernel<M, NU, TXv, TYv, true, false><<<n, WG, 0, s>>>(a, first, owner);  \
-        else stage_kernel<M, NU, TXv, TYv, false, true><<<n, WG, 0, s>>>(a, first, owner);          \
+        if (h1 && h2) stage_kernel<M, NU, TXv, TYv, true, true><<<n, 64 * STAGE_W, 0, s>>>(a, first, owner);   \
+        else if (h1) stage_kernel<M, NU, TXv, TYv, true, false><<<n, 64 * STAGE_W, 0, s>>>(a, first, owner);  \
+        else stage_kernel<M, NU, TXv, TYv, false, true><<<n, 64 * STAGE_W, 0, s>>>(a, first, owner);          \
     } while (0)
     if (tile_w == 32) JANC_STAGE(32, 8);
     else if (tile_w == 64) JANC_STAGE(64, 4);
