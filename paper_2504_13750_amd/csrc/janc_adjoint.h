@@ -13,15 +13,12 @@
 //      alpha_x = max(|u|+c), alpha_y = max(|v|+c) and their argmax (lowest
 //      linear index among equal maxima): block maxima, then one workgroup per
 //      stage input;
-//   B  per interface and component: mu_Fhat = b dt (mu_right - mu_left)/dx and
-//      the reverse of both WENO5 reconstructions (5 + 5 weights), the six
-//      stencil states and their split fluxes formed in place;
-//   C  per interior cell (x and y sweeps on two threads): gather of the
-//      split-flux adjoints of its own strip positions and of the ghost positions
-//      that copy or mirror it from the 5 + 5 interfaces that read them, reverse
-//      of the split (flux Jacobian and the alpha term), the explicit Arrhenius
-//      source (one-step model), the RK bookkeeping, block partials of d/dalpha,
-//      d/dQ, d/dEa;
+//   B  per tile of 64 cells: mu_Fhat = b dt (mu_right - mu_left)/dx and the reverse of
+//      both WENO5 reconstructions of every interface that the tile's cells read;
+//   C  per cell of the tile: gather of the split-flux adjoints of its own strip positions
+//      and of the ghost positions that copy or mirror it, reverse of the split (flux
+//      Jacobian and the alpha term), the explicit Arrhenius source (one-step model), the
+//      RK bookkeeping, per-tile partials of d/dalpha, d/dQ, d/dEa;
 //   D  one workgroup: the partials summed in a fixed order, the alpha adjoints
 //      applied at the argmax cells, theta, and the loss seed of the step start.
 // The temperature of the detailed model is the Newton root of e(T, Y) = e; it is
@@ -61,6 +58,15 @@ __device__ inline long long usrc(const AdjGrid& g, int i, int j, unsigned& fl) {
         }
     }
     return (long long)j * g.nx + i;
+}
+
+// Does cell `at` of a line of len cells own ghost k (0: next to the grid) of side 0 (low)
+// or 1 (high)? Zero-gradient and Dirichlet ghosts belong to the last cell (a Dirichlet
+// row's alpha and Q parts have to be counted once), a slip wall's to its mirror image.
+__device__ __forceinline__ bool owns_ghost(int bc, int at, int len, int side, int k) {
+    if (bc == BC_PERIODIC) return false;
+    const int edge = side ? len - 1 : 0;
+    return at == (bc == BC_SLIPWALL ? (side ? edge - k : k) : edge);
 }
 
 // The cell loads are issued unconditionally (index clamped) so that the loads of
@@ -269,14 +275,16 @@ __device__ __forceinline__ void weno5_adj(double a, double b, double c, double d
     const double s0 = WENO_EPS + ((13.0 / 12.0) * t0 * t0 + 0.25 * u0 * u0);
     const double s1 = WENO_EPS + ((13.0 / 12.0) * t1 * t1 + 0.25 * u1 * u1);
     const double s2 = WENO_EPS + ((13.0 / 12.0) * t2 * t2 + 0.25 * u2 * u2);
-    const double al0 = 0.1 / (s0 * s0), al1 = 0.6 / (s1 * s1), al2 = 0.3 / (s2 * s2);
-    const double S = al0 + al1 + al2;
-    const double w0 = al0 / S, w1 = al1 / S, w2 = al2 / S;
+    // s >= eps and the sum of the weights is a normal number: four reciprocals for ten divisions
+    const double i0 = quotient(1.0, s0), i1 = quotient(1.0, s1), i2 = quotient(1.0, s2);
+    const double al0 = 0.1 * (i0 * i0), al1 = 0.6 * (i1 * i1), al2 = 0.3 * (i2 * i2);
+    const double iS = quotient(1.0, al0 + al1 + al2);
+    const double w0 = al0 * iS, w1 = al1 * iS, w2 = al2 * iS;
     const double f = w0 * q0 + w1 * q1 + w2 * q2;
     const double qb0 = fb * w0, qb1 = fb * w1, qb2 = fb * w2;
-    const double fs = fb / S;
+    const double fs = fb * iS;
     const double ab0 = fs * (q0 - f), ab1 = fs * (q1 - f), ab2 = fs * (q2 - f);
-    const double bb0 = -2.0 * ab0 * al0 / s0, bb1 = -2.0 * ab1 * al1 / s1, bb2 = -2.0 * ab2 * al2 / s2;
+    const double bb0 = -2.0 * ab0 * (al0 * i0), bb1 = -2.0 * ab1 * (al1 * i1), bb2 = -2.0 * ab2 * (al2 * i2);
     const double tb0 = bb0 * (13.0 / 6.0) * t0, ub0 = bb0 * 0.5 * u0;
     const double tb1 = bb1 * (13.0 / 6.0) * t1, ub1 = bb1 * 0.5 * u1;
     const double tb2 = bb2 * (13.0 / 6.0) * t2, ub2 = bb2 * 0.5 * u2;
@@ -348,337 +356,405 @@ __global__ __launch_bounds__(AWG) void adj_alpha(AlphaArgs P) {
     }
 }
 
-// Split flux of component f at a stencil point (the forward's own formula).
-template <int NU>
-__device__ __forceinline__ void split_flux(const double (&V)[NU], double vn, double p, int f,
-                                           bool xdir, double al, double& Fp, double& Fm) {
-    double F = V[f] * vn;
-    if (f == (xdir ? 1 : 2)) F += p;
-    if (f == 3) F = (V[f] + p) * vn;
-    Fp = 0.5 * (F + al * V[f]);
-    Fm = 0.5 * (F - al * V[f]);
-}
-
-// B: per interface and component, mu_Fhat = b dt (mu_right - mu_left)/dx and
-// the reverse of both WENO5 reconstructions; the six stencil states and their
-// split fluxes are formed here from the stage input (component F = blockIdx.y). F is
-// a run-time value, uniform over the workgroup: one body serves every component (a
-// body per component made the kernel of the 12-field model copy its arguments to
-// scratch memory, 304 bytes per lane, written by every thread at entry).
-template <int M, int NU>
-__device__ __forceinline__ void iface_component(const AdjArgs& A, int q, const int F) {
-    const AdjGrid& g = A.g;
-    const int nix = (g.nx + 1) * g.ny, niy = g.twod ? g.nx * (g.ny + 1) : 0;
-    if (q >= nix + niy) return;
-    const bool xdir = q < nix;
-    int r, i0, j0, k, len, lidx;
-    if (xdir) {
-        r = q;
-        j0 = q / (g.nx + 1);
-        k = q - j0 * (g.nx + 1);
-        i0 = k - 3;
-        len = g.nx;
-        lidx = j0 * g.nx + k;
-    } else {
-        r = q - nix;
-        k = r / g.nx;
-        i0 = r - k * g.nx;
-        j0 = k - 3;
-        len = g.ny;
-        lidx = k * g.nx + i0;
-    }
-    const long long lstep = xdir ? 1 : g.nx;
-    const double al = A.alpha[xdir ? 0 : 1];
-    const double ih = xdir ? g.idx : g.idy;
-    const double lr = A.lamW[(size_t)F * A.n + ((k < len) ? lidx : 0)];
-    const double ll = A.lamW[(size_t)F * A.n + ((k > 0) ? lidx - lstep : 0)];
-    const double mr = (k < len) ? lr : 0.0;
-    const double ml = (k > 0) ? ll : 0.0;
-    const double fb = A.b * A.dt * (mr - ml) * ih;
-    // stencil points t = 0..5 at positions k-3 .. k+2 along the sweep
-    DevDomain D{};
-    D.gamma = g.gamma;
-    D.Q = g.Q;
-    double Fp[6], Fm[6];
-#pragma unroll
-    for (int t = 0; t < 6; ++t) {
-        unsigned fl;
-        const long long src = xdir ? usrc(g, i0 + t, j0, fl) : usrc(g, i0, j0 + t, fl);
-        double V[NU], T, vx, vy, p;
-        load_src<M, NU>(A, src, fl, V, T);
-        halo_prims<M, NU>(V, T, D, cmech(A.mech), vx, vy, p);
-        split_flux<NU>(V, xdir ? vx : vy, p, F, xdir, al, Fp[t], Fm[t]);
-    }
-    double gp[5], gm[5];
-    weno5_adj(Fp[0], Fp[1], Fp[2], Fp[3], Fp[4], fb, gp);
-    weno5_adj(Fm[5], Fm[4], Fm[3], Fm[2], Fm[1], fb, gm);
-    const int ni = xdir ? nix : niy;
-    double* out = (xdir ? A.cx : A.cy) + (size_t)F * 10 * ni;
-#pragma unroll
-    for (int m = 0; m < 5; ++m) {
-        out[(size_t)m * ni + r] = gp[m];
-        out[(size_t)(5 + m) * ni + r] = gm[4 - m];
-    }
-}
-
-template <int M, int NU>
-__global__ __launch_bounds__(AWG) void adj_iface(AdjArgs A) {
-    const int q = blockIdx.x * AWG + threadIdx.x;
-    iface_component<M, NU>(A, q, (int)blockIdx.y);
-}
-
-// Gather of the split-flux adjoints of strip position xi (x sweep: row j, xi in
-// 0..nx+5) or yj (y sweep: column i, yj in 0..ny+5) from the 5 + 5 interfaces
-// whose stencils read it.
-template <int NU>
-__device__ __forceinline__ void gather_strip(const AdjArgs& A, bool xdir, int i, int j, int xi,
-                                             double (&mp)[NU], double (&mm)[NU]) {
-    const AdjGrid& g = A.g;
-    const int len = xdir ? g.nx : g.ny;
-    const int ni = xdir ? (g.nx + 1) * g.ny : g.nx * (g.ny + 1);
-#pragma unroll
-    for (int f = 0; f < NU; ++f) {
-        const double* cf = (xdir ? A.cx : A.cy) + (size_t)f * 10 * ni;
-        double ap = 0.0, am = 0.0;
-#pragma unroll
-        for (int m = 0; m < 5; ++m) {
-            // loads at clamped interfaces, then a select: all ten are in flight together
-            const int Ip = xi - m, Im = xi - 1 - m;
-            const bool okp = Ip >= 0 && Ip <= len, okm = Im >= 0 && Im <= len;
-            const int Ipc = okp ? Ip : 0, Imc = okm ? Im : 0;
-            const int rp = xdir ? j * (g.nx + 1) + Ipc : Ipc * g.nx + i;
-            const int rm = xdir ? j * (g.nx + 1) + Imc : Imc * g.nx + i;
-            const double vp = cf[(size_t)m * ni + rp], vm = cf[(size_t)(5 + m) * ni + rm];
-            ap += okp ? vp : 0.0;
-            am += okm ? vm : 0.0;
-        }
-        mp[f] = ap;
-        mm[f] = am;
-    }
-}
-
 // Reverse of the split at one strip state V: flux Jacobian (rows: mass, normal and
-// tangential momentum, energy, species) and the alpha term.
+// tangential momentum, energy, species) and the alpha term. mp(f), mm(f): the gathered
+// adjoints of the split fluxes F+ and F- of component f at the position.
 // out = adjoint of V; pal = d/dalpha part; pQ = d/dQ part.
-template <int NU>
+template <int NU, class Fp, class Fm>
 __device__ __forceinline__ void split_vjp(const double (&V)[NU], const PState<NU>& P, bool xdir,
-                                          double al, const double (&mp)[NU], const double (&mm)[NU],
-                                          double (&out)[NU], double& pal, double& pQ) {
-    double a[NU], bq[NU];
-#pragma unroll
-    for (int f = 0; f < NU; ++f) {
-        a[f] = 0.5 * (mp[f] + mm[f]);
-        bq[f] = 0.5 * (mp[f] - mm[f]);
-    }
-    const double ir = 1.0 / V[0];
-    const int nm = xdir ? 1 : 2, tm = xdir ? 2 : 1;
+                                          double al, Fp&& mp, Fm&& mm, double (&out)[NU], double& pal,
+                                          double& pQ) {
+    const double ir = quotient(1.0, V[0]);
     // normal velocity w, tangential t
     const double w = xdir ? P.u : P.v, t = xdir ? P.v : P.u;
-    const double a_nm = a[nm], a_tm = a[tm], a_E = a[3];
+    const double a1 = 0.5 * (mp(1) + mm(1)), a2 = 0.5 * (mp(2) + mm(2));
+    const double a_0 = 0.5 * (mp(0) + mm(0)), a_E = 0.5 * (mp(3) + mm(3));
+    const double a_nm = xdir ? a1 : a2, a_tm = xdir ? a2 : a1;
     double sr = 0.0;   // sum over the species rows of a_k (rho Y_k)
-#pragma unroll
-    for (int k = 4; k < NU; ++k) sr += a[k] * V[k];
-    const double Ep = (V[3] + P.p) * ir;
+    pal = 0.0;
     const double kp = a_nm + a_E * w;   // weight of dp/dV: normal momentum and energy rows
 #pragma unroll
-    for (int f = 0; f < NU; ++f) out[f] = kp * P.dp[f];
-    out[0] += -a_nm * w * w - a_tm * w * t - a_E * Ep * w - sr * w * ir;
-    out[nm] += a[0] + 2.0 * a_nm * w + a_tm * t + a_E * Ep + sr * ir;
-    out[tm] += a_tm * w;
-    out[3] += a_E * w;
-#pragma unroll
-    for (int k = 4; k < NU; ++k) out[k] += a[k] * w;
-    pal = 0.0;
-#pragma unroll
     for (int f = 0; f < NU; ++f) {
-        out[f] += al * bq[f];
-        pal += V[f] * bq[f];
+        const double p = mp(f), m = mm(f), bq = 0.5 * (p - m);
+        out[f] = kp * P.dp[f] + al * bq;
+        pal += V[f] * bq;
+        if (f >= 4) {
+            const double a = 0.5 * (p + m);
+            sr += a * V[f];
+            out[f] += a * w;
+        }
     }
+    const double Ep = (V[3] + P.p) * ir;
+    out[0] += -a_nm * w * w - a_tm * w * t - a_E * Ep * w - sr * w * ir;
+    const double on = a_0 + 2.0 * a_nm * w + a_tm * t + a_E * Ep + sr * ir, ot = a_tm * w;
+    out[1] += xdir ? on : ot;
+    out[2] += xdir ? ot : on;
+    out[3] += a_E * w;
     pQ = kp * P.dpQ;
 }
 
-// The split-flux adjoints mp, mm gathered at a strip position, applied to the state
-// there (the cell src, mirrored by fl, or a Dirichlet row): out (if add), the alpha
-// and Q parts.
-template <int M, int NU>
+// The adjoints gathered at a strip position, applied to the state there (the cell,
+// mirrored by fl, or Dirichlet row -1 - src): the adjoint of the cell in out (zero for a
+// Dirichlet row), the alpha and Q parts.
+template <int M, int NU, class Fp, class Fm>
 __device__ __forceinline__ void strip_apply(const AdjArgs& A, bool xdir, long long src, unsigned fl,
-                                            const double (&Vc)[NU], double Tc, const double (&mp)[NU],
-                                            const double (&mm)[NU], double (&out)[NU], bool add,
-                                            double& pal, double& pQ) {
+                                            double (&V)[NU], double T, Fp&& mp, Fm&& mm,
+                                            double (&out)[NU], double& pal, double& pQ) {
     const AdjGrid& g = A.g;
-    double Vs[NU], Ts = Tc;
-    if (src >= 0) {
-#pragma unroll
-        for (int f = 0; f < NU; ++f) Vs[f] = Vc[f];
-        if (fl & 1u) Vs[1] = -Vs[1];
-        if (fl & 2u) Vs[2] = -Vs[2];
-    } else {
+    if (src < 0) {
         const double* row = g.dirU + (size_t)(-src - 1) * (MAXF + 1);
 #pragma unroll
-        for (int f = 0; f < NU; ++f) Vs[f] = row[f];
-        Ts = row[MAXF];
+        for (int f = 0; f < NU; ++f) V[f] = row[f];
+        T = row[MAXF];
     }
-    double o[NU], pa, pq;
+    if (fl & 1u) V[1] = -V[1];
+    if (fl & 2u) V[2] = -V[2];
+    double pa, pq;
     PState<NU> P;
-    pstate<M, NU, false>(g, cmech(A.mech), Vs, Ts, P);
-    split_vjp<NU>(Vs, P, xdir, A.alpha[xdir ? 0 : 1], mp, mm, o, pa, pq);
-    if (M == ONESTEP && src < 0) {
-        // Dirichlet ghost: its energy depends on Q through the chemical energy rho Y Q
-        const double* row = g.dirU + (size_t)(-src - 1) * (MAXF + 1);
-        pq += o[3] * row[4];
-    }
+    pstate<M, NU, false>(g, cmech(A.mech), V, T, P);
+    split_vjp<NU>(V, P, xdir, A.alpha[xdir ? 0 : 1], mp, mm, out, pa, pq);
+    // Dirichlet ghost: its energy depends on Q through the chemical energy rho Y Q
+    if (M == ONESTEP && src < 0) pq += out[3] * V[4];
     pal += pa;
     pQ += pq;
-    if (add) {
+    if (fl & 1u) out[1] = -out[1];
+    if (fl & 2u) out[2] = -out[2];
+    if (src < 0) {
 #pragma unroll
-        for (int f = 0; f < NU; ++f) {
-            double v = o[f];
-            if ((f == 1 && (fl & 1u)) || (f == 2 && (fl & 2u))) v = -v;
-            out[f] += v;
-        }
+        for (int f = 0; f < NU; ++f) out[f] = 0.0;
     }
 }
 
-// Adjoint of the cell's own strip position and its contributions.
-template <int M, int NU>
-__device__ __forceinline__ void strip_adjoint(const AdjArgs& A, bool xdir, int i, int j, int pos,
-                                              long long src, unsigned fl, const double (&Vc)[NU],
-                                              double Tc, double (&out)[NU], bool add, double& pal,
-                                              double& pQ) {
-    double mp[NU], mm[NU];
-    gather_strip<NU>(A, xdir, i, j, pos, mp, mm);
-    strip_apply<M, NU>(A, xdir, src, fl, Vc, Tc, mp, mm, out, add, pal, pQ);
-}
+// B, C: one stage reversed on a tile of 64 cells (8 x 8, or 64 x 1 of a 1-D grid), one
+// wavefront per conserved component, one lane per cell.
+//   points   velocities and pressure of the tile and of 5 halo layers (cross-shaped) go to
+//            LDS: a cell's adjoint gathers from interfaces up to 3 away, whose stencils
+//            reach 3 further;
+//   sweeps   per direction, each wavefront forms the split fluxes of its component, reverses
+//            both WENO5 of every interface that the tile's cells read (13 per 8 cells: the
+//            5 that neighbouring tiles share are formed by both), and gathers the weights at
+//            the cells' own strip positions and at the ghost positions the cells own. On a
+//            periodic side the strip wraps: the two end interfaces have the same stencil and
+//            the reverse is linear in the adjoint difference, so they are taken as one;
+//   apply    the gathered adjoints of all components meet in LDS; one wavefront each takes
+//            the x positions, the y positions, the explicit source (one-step model) and the
+//            ghost positions of each side through the flux Jacobian (on any of the sides a
+//            cell's ghosts have one state, and the reverse of the split is linear in the
+//            gathered adjoints: they are summed and applied once);
+//   update   wavefront f adds up component f, writes the adjoint of the stage input and
+//            does the RK bookkeeping; per-tile partials of the alpha, Q and E_a adjoints.
+// Bound: latency (an adjoint grid has a few hundred tiles). As two kernels, the interfaces
+// once per component with all fields of all six stencil states re-read for each, and ten
+// weights per interface and component through memory, a reversed stage of the 512 x 64
+// one-step tube took 20 + 13.6 us and of the 128 x 64 9-species front 22 + 31 us.
+template <int TX, int TY>
+struct AdjTile {
+    static constexpr bool TWO = TY > 1;
+    static constexpr int H = 5;
+    static constexpr int NHX = 2 * H * TY, NHY = TWO ? 2 * H * TX : 0;
+    static constexpr int NP = 64 + NHX + NHY, NPL = (NP + 63) / 64, NPP = 64 * NPL;
+    static constexpr int SX = (TX + 2 * H) * TY, SY = TWO ? TX * (TY + 2 * H) : 0;   // strip positions
+    static constexpr int S = SX > SY ? SX : SY;
+    static constexpr int IX = (TX + 5) * TY, IY = TWO ? TX * (TY + 5) : 0;           // interfaces
+    static constexpr int I = IX > IY ? IX : IY, IL = (I + 63) / 64;
+    static constexpr int NTASK = 7;
+    static constexpr int BUF0 = 3 * S + 5 * I;          // F+, F-, lambda strips; half the weights
+    static constexpr int BUF = BUF0 > 12 * 64 ? BUF0 : 12 * 64;
+    static_assert(TX * TY == 64 && NTASK * 64 <= BUF, "tile");
 
-// The ghost positions on one side (0: low, 1: high) of the cell's row (x sweep) or
-// column (y sweep) that this cell owns: those whose source is the cell, or, on the first
-// or last cell, the side's Dirichlet row. All of them have the same state (the same
-// source and mirror flags, or the same row), and the reverse of the split is linear in
-// the gathered adjoints, so their gathers are summed (in position order) and applied
-// once: one state evaluation per side instead of one per position.
-template <int M, int NU>
-__device__ __forceinline__ void ghost_side(const AdjArgs& A, bool xdir, int i, int j, int side,
-                                           long long c, const double (&Vc)[NU], double Tc,
-                                           double (&out)[NU], double& pal, double& pQ) {
+    // tile-local position of point p: own cells, x halo, y halo
+    __device__ static void point(int p, int& li, int& lj) {
+        if (p < 64) {
+            li = p % TX;
+            lj = p / TX;
+        } else if (p < 64 + NHX) {
+            const int h = p - 64, side = h >= H * TY, r = h - side * H * TY;
+            lj = r / H;
+            li = (r - lj * H) + (side ? TX : -H);
+        } else {
+            const int h = p - 64 - NHX, side = h >= H * TX, r = h - side * H * TX;
+            const int row = r / TX;
+            li = r - row * TX;
+            lj = row + (side ? TY : -H);
+        }
+    }
+};
+
+template <bool XDIR> struct SweepDir { static constexpr bool value = XDIR; };
+
+template <int M, int NU, int TX, int TY>
+__global__ __launch_bounds__(64 * NU) void adj_tile(AdjArgs A) {
+    using G = AdjTile<TX, TY>;
+    constexpr int NPL = G::NPL, NPP = G::NPP;
+    static_assert(NU >= 5 && 64 * NU >= NPP, "one point per thread");
+    __shared__ double smem[3 * NPP + NU * G::BUF + NU * 4];
+    __shared__ int psrc[NPP];
+    __shared__ unsigned pflag[NPP];
+    double* pu = smem;
+    double* pv = pu + NPP;
+    double* pp = pv + NPP;
+    double* bufs = pp + NPP;
+    double* part = bufs + NU * G::BUF;
     const AdjGrid& g = A.g;
-    const int len = xdir ? g.nx : g.ny;
-    const int own = xdir ? i : j;
-    double mp[NU], mm[NU];
-#pragma unroll
-    for (int f = 0; f < NU; ++f) mp[f] = mm[f] = 0.0;
-    bool any = false;
-    long long s0 = 0;
-    unsigned f0 = 0u;
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        const int gp = (side == 0) ? -1 - k : len + k;
-        unsigned fl;
-        const long long s = xdir ? usrc(g, gp, j, fl) : usrc(g, i, gp, fl);
-        const bool owner = (s == c) || (s < 0 && own == ((side == 0) ? 0 : len - 1));
-        if (owner) {
-            double ap[NU], am[NU];
-            gather_strip<NU>(A, xdir, xdir ? gp : i, xdir ? j : gp, gp + 3, ap, am);
-#pragma unroll
-            for (int f = 0; f < NU; ++f) {
-                mp[f] += ap[f];
-                mm[f] += am[f];
-            }
-            any = true;
-            s0 = s;
-            f0 = fl;
-        }
-    }
-    if (any) strip_apply<M, NU>(A, xdir, s0, f0, Vc, Tc, mp, mm, out, s0 == c, pal, pQ);
-}
+    const int tid = threadIdx.x, l = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int ntx = (g.nx + TX - 1) / TX;
+    const int ty = (int)blockIdx.x / ntx, x0 = ((int)blockIdx.x - ty * ntx) * TX, y0 = ty * TY;
+    const bool perx = g.bc[0] == BC_PERIODIC, pery = g.twod && g.bc[2] == BC_PERIODIC;
 
-// C: per interior cell, the adjoint of the stage input: its own x and y strip
-// positions, the ghost positions that copy or mirror it (and, on the first or
-// last cell of a row or column, the Dirichlet ghosts of that side), the
-// explicit Arrhenius source (one-step model) and the RK bookkeeping; per-block
-// partials of the alpha, Q and Ea adjoints. Two threads per cell: the first half of
-// the workgroup takes the x sweep, the second half the y sweep, and the y part
-// reaches the cell's thread through LDS.
-constexpr int CPB = AWG / 2;
-
-template <int M, int NU>
-__global__ __launch_bounds__(AWG) void adj_cell(AdjArgs A) {
-    __shared__ double sh[8];
-    __shared__ double ysum[NU][CPB];
-    const int lc = threadIdx.x % CPB;
-    const bool ydir = threadIdx.x >= CPB;
-    const long long c = (long long)blockIdx.x * CPB + lc;
-    const AdjGrid& g = A.g;
-    double pax = 0.0, pay = 0.0, pQ = 0.0, pEa = 0.0;
-    double V[NU], out[NU], Tc = 0.0;
-#pragma unroll
-    for (int f = 0; f < NU; ++f) out[f] = 0.0;
-    const int j = (int)(c / g.nx), i = (int)(c - (long long)j * g.nx);
-    if (c < A.n) {
-#pragma unroll
-        for (int f = 0; f < NU; ++f) V[f] = A.V[(size_t)f * A.n + c];
-        if (M == DETAILED) Tc = A.VT[c];
-        if (!ydir) {
-#pragma unroll
-            for (int f = 0; f < NU; ++f) out[f] = A.b * A.lamW[(size_t)f * A.n + c];
-            strip_adjoint<M, NU>(A, true, i, j, i + 3, c, 0u, V, Tc, out, true, pax, pQ);
-            if (i < 3 || i >= g.nx - 3) {
-                ghost_side<M, NU>(A, true, i, j, 0, c, V, Tc, out, pax, pQ);
-                ghost_side<M, NU>(A, true, i, j, 1, c, V, Tc, out, pax, pQ);
-            }
-        } else if (g.twod) {
-            strip_adjoint<M, NU>(A, false, i, j, j + 3, c, 0u, V, Tc, out, true, pay, pQ);
-            if (j < 3 || j >= g.ny - 3) {
-                ghost_side<M, NU>(A, false, i, j, 0, c, V, Tc, out, pay, pQ);
-                ghost_side<M, NU>(A, false, i, j, 1, c, V, Tc, out, pay, pQ);
-            }
+    // ---- points
+    if (tid < NPP) {
+        int li, lj;
+        G::point(tid < G::NP ? tid : 0, li, lj);
+        const int i = x0 + li, j = y0 + lj;
+        const bool inx = i >= 0 && i < g.nx, iny = j >= 0 && j < g.ny;
+        // positions in the strips: the grid, three ghost layers, all of a periodic wrap
+        const bool ok = (inx && iny) || (iny && (perx || (i >= -3 && i < g.nx + 3))) ||
+                        (inx && g.twod && (pery || (j >= -3 && j < g.ny + 3)));
+        long long s = 0;
+        unsigned fl = 0u;
+        if (ok) {
+            s = usrc(g, i, j, fl);
+            if ((inx || perx) && (iny || pery)) fl |= 8u;   // has an adjoint of its own
+            if (s < 0) fl |= 4u;
         }
-    }
-    if (ydir) {
-#pragma unroll
-        for (int f = 0; f < NU; ++f) ysum[f][lc] = out[f];
+        double V[NU], T, vx, vy, pr;
+        load_src<M, NU>(A, s, fl, V, T);
+        DevDomain D{};
+        D.gamma = g.gamma;
+        D.Q = g.Q;
+        halo_prims<M, NU>(V, T, D, cmech(A.mech), vx, vy, pr);
+        pu[tid] = vx;
+        pv[tid] = vy;
+        pp[tid] = pr;
+        psrc[tid] = (int)(s < 0 ? -s - 1 : s);
+        pflag[tid] = fl;
     }
     __syncthreads();
-    if (!ydir && c < A.n) {
+
+    // ---- sweeps: component w
+    const int cli = l % TX, clj = l / TX, ci = x0 + cli, cj = y0 + clj;
+    const bool cell = ci < g.nx && cj < g.ny;
+    const long long c = (long long)cj * g.nx + ci;
+    const bool gl[4] = {!perx && x0 == 0, !perx && x0 + TX > g.nx - 3, g.twod && !pery && y0 == 0,
+                        g.twod && !pery && y0 + TY > g.ny - 3};   // sides with ghosts owned here
+    double* buf = bufs + w * G::BUF;
+    double own[4] = {0.0, 0.0, 0.0, 0.0};       // x F+, x F-, y F+, y F- at the cell
+    double gh[8];                               // the same at its ghosts: W, E, S, N
 #pragma unroll
-        for (int f = 0; f < NU; ++f) out[f] += ysum[f][lc];
-        if constexpr (M == ONESTEP) {
-            // explicit source S4 = -k r exp(-Ea/T), T = p/(rho R)
-            PState<NU> P;
-            pstate<M, NU, false>(g, nullptr, V, 0.0, P);
-            const double mu4 = A.b * A.dt * A.lamW[(size_t)4 * A.n + c];
-            const double T = P.p / (V[0] * g.R);
-            const double ex = exp(-g.Ea / T);
-            const double S = -g.k * V[4] * ex;
-            const double dSdT = S * g.Ea / (T * T);
-            const double iRr = 1.0 / (V[0] * g.R);
-            double dT[NU];
+    for (int k = 0; k < 8; ++k) gh[k] = 0.0;
+    {
+        double u[NPL], lam[NPL];
 #pragma unroll
-            for (int f = 0; f < NU; ++f) dT[f] = P.dp[f] * iRr;
-            dT[0] -= P.p / V[0] * iRr;
-#pragma unroll
-            for (int f = 0; f < NU; ++f) out[f] += mu4 * dSdT * dT[f];
-            out[4] += mu4 * (-g.k * ex);
-            pQ += mu4 * dSdT * (P.dpQ * iRr);
-            pEa = mu4 * (-S / T);
+        for (int q = 0; q < NPL; ++q) {
+            const int s = psrc[64 * q + l];
+            const unsigned fl = pflag[64 * q + l];
+            const double* F = (fl & 4u) ? g.dirU + (size_t)s * (MAXF + 1) + w : A.V + (size_t)w * A.n + s;
+            u[q] = *F;
+            lam[q] = (fl & 8u) ? A.lamW[(size_t)w * A.n + s] : 0.0;
+            if ((w == 1 && (fl & 1u)) || (w == 2 && (fl & 2u))) u[q] = -u[q];
         }
+        auto sweep = [&](auto xd) {
+            constexpr bool X = decltype(xd)::value;
+            constexpr int NS = X ? G::SX : G::SY;           // strip positions
+            constexpr int ST = X ? 1 : TX;                  // stride along the sweep
+            constexpr int NI = X ? G::IX : G::IY;
+            constexpr int LEN = (X ? TX : TY) + 5;          // interfaces per line
+            double* P = buf;
+            double* Mn = P + NS;
+            double* La = Mn + NS;
+            double* Wt = La + NS;
+            const double al = A.alpha[X ? 0 : 1], ih = X ? g.idx : g.idy;
+            const int len = X ? g.nx : g.ny, o0 = X ? x0 : y0;
+            const bool per = X ? perx : pery;
 #pragma unroll
-        for (int f = 0; f < NU; ++f) {
-            A.lamOut[(size_t)f * A.n + c] = out[f];
-            const double lw = A.a * A.lamW[(size_t)f * A.n + c];
-            double acc = A.init_acc ? lw : A.acc[(size_t)f * A.n + c] + lw;
-            if (A.add_out) acc += out[f];
-            A.acc[(size_t)f * A.n + c] = acc;
+            for (int q = 0; q < NPL; ++q) {
+                const int p = 64 * q + l;
+                if (p < 64 || (X ? p < 64 + G::NHX : (p >= 64 + G::NHX && p < G::NP))) {
+                    int li, lj;
+                    G::point(p, li, lj);
+                    const int o = X ? lj * (TX + 2 * G::H) + li + G::H : (lj + G::H) * TX + li;
+                    const double vn = X ? pu[p] : pv[p];
+                    double F = u[q] * vn;
+                    if (w == (X ? 1 : 2)) F += pp[p];
+                    if (w == 3) F = (u[q] + pp[p]) * vn;
+                    P[o] = 0.5 * (F + al * u[q]);
+                    Mn[o] = 0.5 * (F - al * u[q]);
+                    La[o] = lam[q];
+                }
+            }
+            wave_sync();
+            double gm[G::IL][5];
+#pragma unroll
+            for (int q = 0; q < G::IL; ++q) {
+                const int it = 64 * q + l;
+#pragma unroll
+                for (int m = 0; m < 5; ++m) gm[q][m] = 0.0;
+                if (it < NI) {
+                    const int kk = X ? it % LEN : it / TX, line = X ? it / LEN : it % TX;
+                    const int k = o0 - 2 + kk;              // interface left of cell k
+                    const int o = X ? line * (TX + 2 * G::H) + kk + 3 : (kk + 3) * TX + line;
+                    double gp[5];
+#pragma unroll
+                    for (int m = 0; m < 5; ++m) gp[m] = 0.0;
+                    if (per || (k >= 0 && k <= len)) {
+                        const double fb = A.b * A.dt * (La[o] - La[o - ST]) * ih;
+                        const double* p = P + o;
+                        const double* n = Mn + o;
+                        double gr[5];
+                        weno5_adj(p[-3 * ST], p[-2 * ST], p[-ST], p[0], p[ST], fb, gp);
+                        weno5_adj(n[2 * ST], n[ST], n[0], n[-ST], n[-2 * ST], fb, gr);
+#pragma unroll
+                        for (int m = 0; m < 5; ++m) gm[q][m] = gr[4 - m];
+                    }
+#pragma unroll
+                    for (int m = 0; m < 5; ++m) Wt[m * NI + it] = gp[m];
+                }
+            }
+            wave_sync();
+            // sum over the five interfaces whose F+ (shift 5) or F- (shift 4) stencil holds the
+            // position `at` of this lane's line
+            const int line = X ? clj : cli;
+            auto gather = [&](int at, int shift) {
+                double r = 0.0;
+#pragma unroll
+                for (int m = 0; m < 5; ++m) {
+                    const int kk = at + shift - m;
+                    if (kk >= 0 && kk < LEN) r += Wt[m * NI + (X ? line * LEN + kk : kk * TX + line)];
+                }
+                return r;
+            };
+            const int me = X ? cli : clj, ca = X ? ci : cj;
+            auto ghosts = [&](int side, int shift) {
+                double r = 0.0;
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    const int gp = (side == 0) ? -1 - k : len + k;
+                    if (owns_ghost(g.bc[(X ? 0 : 2) + side], ca, len, side, k)) r += gather(gp - o0, shift);
+                }
+                return r;
+            };
+            constexpr int B = X ? 0 : 2;
+            own[B] = gather(me, 5);
+            if (gl[B]) gh[2 * B] = ghosts(0, 5);
+            if (gl[B + 1]) gh[2 * B + 2] = ghosts(1, 5);
+            wave_sync();
+#pragma unroll
+            for (int q = 0; q < G::IL; ++q) {
+                const int it = 64 * q + l;
+                if (it < NI)
+#pragma unroll
+                    for (int m = 0; m < 5; ++m) Wt[m * NI + it] = gm[q][m];
+            }
+            wave_sync();
+            own[B + 1] = gather(me, 4);
+            if (gl[B]) gh[2 * B + 1] = ghosts(0, 4);
+            if (gl[B + 1]) gh[2 * B + 3] = ghosts(1, 4);
+            wave_sync();
+        };
+        sweep(SweepDir<true>{});
+        if constexpr (G::TWO) sweep(SweepDir<false>{});
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) buf[64 * k + l] = own[k];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) buf[64 * (4 + k) + l] = gh[k];
+    __syncthreads();
+
+    // ---- apply: task 0 / 1 the x / y positions, 2 the source, 3 + s the ghosts of side s
+    constexpr int TL = (G::NTASK + NU - 1) / NU;
+    double out[TL][NU];
+    double pa[2] = {0.0, 0.0}, pQ = 0.0, pEa = 0.0;
+#pragma unroll
+    for (int k = 0; k < TL; ++k) {
+        const int t = w + NU * k;
+#pragma unroll
+        for (int f = 0; f < NU; ++f) out[k][f] = 0.0;
+        const bool on = t == 0 || (t == 1 && g.twod) || (t == 2 && M == ONESTEP) || (t >= 3 && t < G::NTASK && gl[t - 3]);
+        if (on && cell) {
+            double V[NU], Tc = 0.0;
+#pragma unroll
+            for (int f = 0; f < NU; ++f) V[f] = A.V[(size_t)f * A.n + c];
+            if (M == DETAILED) Tc = A.VT[c];
+            if (t == 2) {
+                if constexpr (M == ONESTEP) {
+                    // explicit source S4 = -k r exp(-Ea/T), T = p/(rho R)
+                    PState<NU> P;
+                    pstate<M, NU, false>(g, nullptr, V, 0.0, P);
+                    const double mu4 = A.b * A.dt * A.lamW[(size_t)4 * A.n + c];
+                    const double T = P.p / (V[0] * g.R);
+                    const double ex = exp(-g.Ea / T);
+                    const double S = -g.k * V[4] * ex;
+                    const double dSdT = S * g.Ea / (T * T);
+                    const double iRr = 1.0 / (V[0] * g.R);
+                    double dT[NU];
+#pragma unroll
+                    for (int f = 0; f < NU; ++f) dT[f] = P.dp[f] * iRr;
+                    dT[0] -= P.p / V[0] * iRr;
+#pragma unroll
+                    for (int f = 0; f < NU; ++f) out[k][f] = mu4 * dSdT * dT[f];
+                    out[k][4] += mu4 * (-g.k * ex);
+                    pQ += mu4 * dSdT * (P.dpQ * iRr);
+                    pEa = mu4 * (-S / T);
+                }
+            } else {
+                const bool xd = t == 0 || t == 3 || t == 4;
+                long long src = c;
+                unsigned fl = 0u;
+                bool any = true;
+                if (t >= 3) {
+                    const int side = (t - 3) & 1, len = xd ? g.nx : g.ny;
+                    any = false;
+                    for (int q = 2; q >= 0; --q)
+                        if (owns_ghost(g.bc[t - 3], xd ? ci : cj, len, side, q)) {
+                            const int gp = side ? len + q : -1 - q;
+                            src = xd ? usrc(g, gp, cj, fl) : usrc(g, ci, gp, fl);
+                            any = true;
+                        }
+                }
+                const int r = t < 2 ? 2 * t : 4 + 2 * (t - 3);
+                const double* R = bufs + 64 * r + l;
+                if (any)
+                    strip_apply<M, NU>(A, xd, src, fl, V, Tc, [&](int f) { return R[f * G::BUF]; },
+                                       [&](int f) { return R[f * G::BUF + 64]; }, out[k], pa[xd ? 0 : 1], pQ);
+            }
         }
     }
-    const double s0 = block_sum(pax, sh);
-    const double s1 = block_sum(pay, sh);
-    const double s2 = block_sum(pQ, sh);
-    const double s3 = block_sum(pEa, sh);
-    if (threadIdx.x == 0) {
-        A.part[(size_t)blockIdx.x * 4 + 0] = s0;
-        A.part[(size_t)blockIdx.x * 4 + 1] = s1;
-        A.part[(size_t)blockIdx.x * 4 + 2] = s2;
-        A.part[(size_t)blockIdx.x * 4 + 3] = s3;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < TL; ++k) {
+        const int t = w + NU * k;
+        if (t < G::NTASK)
+#pragma unroll
+            for (int f = 0; f < NU; ++f) bufs[(f * G::NTASK + t) * 64 + l] = out[k][f];
+    }
+    double sum[4] = {pa[0], pa[1], pQ, pEa};
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) sum[k] += __shfl_xor(sum[k], o, 64);
+    if (l == 0)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) part[4 * w + k] = sum[k];
+    __syncthreads();
+
+    // ---- update: component w of the cell
+    if (cell) {
+        const size_t at = (size_t)w * A.n + c;
+        const double lw = A.lamW[at];
+        double o = A.b * lw;
+#pragma unroll
+        for (int t = 0; t < G::NTASK; ++t) o += bufs[(w * G::NTASK + t) * 64 + l];
+        A.lamOut[at] = o;
+        double acc = A.a * lw;
+        if (!A.init_acc) acc = A.acc[at] + acc;
+        if (A.add_out) acc += o;
+        A.acc[at] = acc;
+    }
+    if (tid < 4) {
+        double t = 0.0;
+        for (int q = 0; q < NU; ++q) t += part[4 * q + tid];
+        A.part[(size_t)blockIdx.x * 4 + tid] = t;
     }
 }
 

@@ -31,18 +31,29 @@ __global__ __launch_bounds__(AWG) void adj_alpha_reduce(AlphaArgs P) {
     }
 }
 
-__global__ void adj_loss_sum(const double* term, int nsteps, double* loss) {
-    if (threadIdx.x != 0) return;
+// Sum of v[0 .. n) in index order by one wavefront: its lanes load 64 values at a time and
+// lane 0 adds them up (one lane that also loaded them waited for memory at every value).
+__device__ __forceinline__ double ordered_sum(const double* v, int n) {
+    __shared__ double sh[64];
     double s = 0.0;
-    for (int q = 0; q < nsteps; ++q) s += term[q];
-    loss[0] = s;
+    for (int b = 0; b < n; b += 64) {
+        __syncthreads();
+        if (b + (int)threadIdx.x < n) sh[threadIdx.x] = v[b + threadIdx.x];
+        __syncthreads();
+        if (threadIdx.x == 0)
+            for (int q = 0; q < min(64, n - b); ++q) s += sh[q];
+    }
+    return s;
+}
+
+__global__ void adj_loss_sum(const double* term, int nsteps, double* loss) {
+    const double s = ordered_sum(term, nsteps);
+    if (threadIdx.x == 0) loss[0] = s;
 }
 
 __global__ void adj_chain_sum(const double* part, int nb, double* theta) {
-    if (threadIdx.x != 0) return;
-    double s = 0.0;
-    for (int q = 0; q < nb; ++q) s += part[q];
-    theta[0] += s;
+    const double s = ordered_sum(part, nb);
+    if (threadIdx.x == 0) theta[0] += s;
 }
 
 // ------------------------------------------------------------------ launchers
@@ -62,14 +73,18 @@ hipError_t adj_alpha_launch(int model, int ns, const AlphaArgs& P, hipStream_t s
     return hipGetLastError();
 }
 
+// Tiles of a grid (workgroups of adj_tile).
+int adj_tile_count(const AdjGrid& g) {
+    return g.twod ? ((g.nx + 7) / 8) * ((g.ny + 7) / 8) : (g.nx + 63) / 64;
+}
+
 hipError_t adj_stage(int model, int ns, const AdjArgs& A, hipStream_t s) {
     if (model != ONESTEP) {
         const SpeciesOps* o = species_ops(ns);
         return o ? o->adj_stage(A, s) : hipErrorInvalidValue;
     }
-    const int ni = (A.g.nx + 1) * A.g.ny + (A.g.twod ? A.g.nx * (A.g.ny + 1) : 0);
-    adj_iface<ONESTEP, 5><<<dim3((ni + AWG - 1) / AWG, 5), AWG, 0, s>>>(A);
-    adj_cell<ONESTEP, 5><<<A.nbd, AWG, 0, s>>>(A);
+    if (A.g.twod) adj_tile<ONESTEP, 5, 8, 8><<<A.nbd, 64 * 5, 0, s>>>(A);
+    else adj_tile<ONESTEP, 5, 64, 1><<<A.nbd, 64 * 5, 0, s>>>(A);
     adj_finish<ONESTEP, 5><<<1, AWG, 0, s>>>(A);
     return hipGetLastError();
 }

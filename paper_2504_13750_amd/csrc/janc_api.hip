@@ -1192,9 +1192,7 @@ janc_status run_adjoint(janc_ctx* c, const janc_grid* g, const janc_physics* ph,
     ag.k = ph->k;
     ag.dirU = P->ddir;
     const int nba = (int)((n + 255) / 256);          // cell blocks of the alpha kernel
-    const int nbd = (int)((n + 127) / 128);          // blocks of the cell kernel (128 cells each)
-    const long long nix = (long long)(g->nx + 1) * g->ny;
-    const long long niy = ag.twod ? (long long)g->nx * (g->ny + 1) : 0;
+    const int nbd = adj_tile_count(ag);              // tiles of the reverse sweep
     const long long nf = (long long)NU * n;          // conserved fields of a state
     const long long sn = det ? nf + n : nf;          // a stored state (+ temperatures)
     const int nsl = 3 * K;                            // stage inputs of one segment
@@ -1216,8 +1214,8 @@ janc_status run_adjoint(janc_ctx* c, const janc_grid* g, const janc_physics* ph,
         sArgm[b] = take((size_t)nsl);
     }
     const Seg sLam = take(nf), sLA = take(nf), sLB = take(nf), sLC = take(nf), sAcc = take(nf),
-              sT0 = take(n), sT1 = take(n), sCx = take(10 * NU * nix), sCy = take(10 * NU * niy),
-              sPart = take(4 * (size_t)nbd + 8), sMisc = take(16), sPc = take(np + 1),
+              sT0 = take(n), sT1 = take(n),
+              sPart = take(4 * (size_t)std::max(nbd, nba) + 8), sMisc = take(16), sPc = take(np + 1),
               sPw = take(np + 1), sTerms = take((size_t)N);
     if (tot > c->adj_doubles) {
         if (c->adj_mem) hipFree(c->adj_mem);
@@ -1354,8 +1352,6 @@ janc_status run_adjoint(janc_ctx* c, const janc_grid* g, const janc_physics* ph,
     A.n = n;
     A.dt = dt;
     A.mech = c->dmech;
-    A.cx = at(sCx);
-    A.cy = at(sCy);
     A.part = at(sPart);
     A.nbd = nbd;
     A.theta = theta;

@@ -63,6 +63,13 @@ __device__ __forceinline__ void after(double& done, double& next) {
     asm volatile("" : "+v"(done), "+v"(next));
 }
 
+// LDS accesses of one wave are executed in order; this keeps the compiler from moving them
+// across the point where lanes read what other lanes of their wave wrote.
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // A value that is the same in every lane, moved to scalar registers.
 __device__ __forceinline__ double uniform(double v) {
     union { double d; int i[2]; } x;

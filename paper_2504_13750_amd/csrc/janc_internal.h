@@ -198,11 +198,10 @@ struct AdjArgs {
     double* acc;              // adjoint of the step start U^n [NU][n]
     double b, a, dt;
     int init_acc, add_out;
-    double *cx, *cy;          // reverse WENO5 weights per interface [NU][10][interfaces]
     const double* alpha;      // [2] alpha_x, alpha_y of the stage input
     const int* argm;          // [2] lowest cell attaining them
-    double* part;             // [nbd][4] block partials
-    int nbd;                  // cell blocks
+    double* part;             // [nbd][4] tile partials
+    int nbd;                  // tiles of 64 cells (adj_tile_count)
     double* theta;            // [2]: dL/dQ, dL/dEa
     const double* seedU;      // state whose probe loss seeds acc after this stage (or null)
     const double* seedT;      // its temperatures (detailed model)
@@ -242,6 +241,7 @@ struct AdjChemArgs {
 
 // model: ONESTEP or DETAILED; ns: species of the detailed model (2 or 9)
 hipError_t adj_alpha_launch(int model, int ns, const AlphaArgs& P, hipStream_t s);
+int adj_tile_count(const AdjGrid& g);
 hipError_t adj_stage(int model, int ns, const AdjArgs& A, hipStream_t s);
 hipError_t adj_chem_launch(int ns, const AdjChemArgs& A, hipStream_t s);
 hipError_t adj_loss_launch(int model, int ns, const AdjGrid& g, const DevMech* mech,

@@ -153,13 +153,6 @@ __device__ __forceinline__ void split_flux(double u, double v, double al, double
     }
 }
 
-// LDS accesses of one wave are executed in order; this keeps the compiler from moving them
-// across the point where lanes read what other lanes of their wave wrote.
-__device__ __forceinline__ void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
 template <int M, int NU, int TX, int TY>
 __device__ __forceinline__ void stage_tile(const StageArgs& a, const int ti, const Tile tile, double* smem) {
     using G = Geom<TX, TY>;

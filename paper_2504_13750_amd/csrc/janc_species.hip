@@ -55,9 +55,8 @@ hipError_t adj_alpha_l(const AlphaArgs& P, hipStream_t s) {
 }
 
 hipError_t adj_stage_l(const AdjArgs& A, hipStream_t s) {
-    const int ni = (A.g.nx + 1) * A.g.ny + (A.g.twod ? A.g.nx * (A.g.ny + 1) : 0);
-    adj_iface<DETAILED, NU><<<dim3((ni + AWG - 1) / AWG, NU), AWG, 0, s>>>(A);
-    adj_cell<DETAILED, NU><<<A.nbd, AWG, 0, s>>>(A);
+    if (A.g.twod) adj_tile<DETAILED, NU, 8, 8><<<A.nbd, 64 * NU, 0, s>>>(A);
+    else adj_tile<DETAILED, NU, 64, 1><<<A.nbd, 64 * NU, 0, s>>>(A);
     adj_finish<DETAILED, NU><<<1, AWG, 0, s>>>(A);
     return hipGetLastError();
 }
