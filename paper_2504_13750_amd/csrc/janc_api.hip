@@ -84,6 +84,7 @@ struct janc_plan {
     long long pool = 0;
     int nunits = 0;
     int tile_w = 16;
+    bool small = false;           // few tiles: the stages run on quarter tiles (small_tiles)
     int linear_sched = 0;         // 1: workgroup b takes tile b; 0: XCD-contiguous tile runs
     bool tuned = false;           // janc_plan_autotune has chosen tile_w and linear_sched
     int kind_mask = 0;            // bit 0: 2-D tiles present, bit 1: 1-D tiles present
@@ -551,6 +552,14 @@ janc_status build_plan(janc_ctx* c, int nd, const janc_domain* doms, int nb, con
 StageArgs base_args(janc_plan* P, const janc_time* tm, double* U, double* T, double* t,
                     double* dt_log, int cap);
 
+// Stages of plans of at most this many tiles run on quarter tiles (four times the workgroups,
+// 1.4 times the work), except with 64 x 4 tiles (a quarter is 8 x 8 cells). Measured, us per
+// step of whole / quarter tiles: 9 species 32 tiles 64 / 48, 64 tiles 65 / 52, 96 tiles 67 / 71;
+// one-step 4 tiles 38 / 28, 64 tiles 38 / 35, 128 tiles 40 / 45; gas without chemistry 8 tiles
+// (2000 x 1) 26.5 / 23.6, 16 tiles 30 / 26, 64 tiles 31 / 33.
+int small_tiles(int model) { return model == CPG ? 32 : 64; }
+int stage_width(const janc_plan* P) { return P->small ? QUARTER_TILES : P->tile_w; }
+
 // Halo source table: for every tile point outside its block or on a coarse-fine ring,
 // the source resolve() gives (level map, block record, coarser level), found once per
 // plan by a kernel so that the stage launches read one word per such point. Plans of
@@ -562,13 +571,14 @@ janc_status build_halo_table(janc_ctx* c, janc_plan* P) {
     P->hstride = 0;
     if (P->arena || (P->flags & JANC_PLAN_RESOLVE_HALOS) || P->pool >= (1ll << 28) || P->htiles.empty())
         return JANC_OK;
-    const int stride = halo_table_stride(P->tile_w, P->kind_mask);
+    const int stride = halo_table_stride(stage_width(P), P->kind_mask);
     int* tab = nullptr;
-    if (janc_status st = dalloc(c, &tab, (size_t)P->htiles.size() * stride)) return st;
+    const size_t rows = P->htiles.size() * (size_t)(P->small ? 4 : 1);
+    if (janc_status st = dalloc(c, &tab, rows * stride)) return st;
     janc_time tm{};
     tm.cfl = 1.0;
     StageArgs a = base_args(P, &tm, nullptr, nullptr, nullptr, nullptr, 0);
-    hipError_t e = launch_halo_table(P->tile_w, a, tab, stride, nullptr);
+    hipError_t e = launch_halo_table(stage_width(P), a, tab, stride, nullptr);
     if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
     if (e != hipSuccess) {
         hipFree(tab);
@@ -605,6 +615,7 @@ janc_status build_tiles(janc_ctx* c, janc_plan* P) {
         }
         P->lev_count[l] = (int)P->htiles.size() - P->lev_first[l];
     }
+    P->small = (int)P->htiles.size() <= small_tiles(c->model) && (TX < 64 || !(P->kind_mask & 1));
     if (P->dtiles && !P->arena) hipFree(P->dtiles);
     P->dtiles = nullptr;
     if (janc_status st = pupload(P, &P->dtiles, P->htiles)) return st;
@@ -747,7 +758,7 @@ hipError_t enqueue_crossover(janc_plan* P, const StageArgs& base, double* U, dou
             a.xfirst = (first && st == 1) ? 1 : 0;
             a.xlast = (l == 0 && st == 3 && model != DETAILED) ? 1 : 0;
             a.xskip_cov = last_of_level ? 1 : 0;
-            e = launch_stage(model, ns, P->kind_mask, P->tile_w, a, P->lev_first[l], n, s);
+            e = launch_stage(model, ns, P->kind_mask, stage_width(P), a, P->lev_first[l], n, s);
             first = false;
         }
         if (e == hipSuccess && model == DETAILED) {
@@ -814,12 +825,12 @@ hipError_t enqueue_step(janc_plan* P, const StageArgs& base, double* U, double* 
         a.reduce_out = (st == 3 && model == DETAILED) ? 0 : 1;
         if (P->flags & JANC_PLAN_PER_BLOCK) {
             for (int id = 0; id < P->nblk && e == hipSuccess; ++id)
-                e = launch_stage(model, ns, P->kind_mask, P->tile_w, a, P->tile_first[id], P->tile_count[id], s);
+                e = launch_stage(model, ns, P->kind_mask, stage_width(P), a, P->tile_first[id], P->tile_count[id], s);
         } else if (P->flags & JANC_PLAN_PER_LEVEL) {
             for (int l = 0; l <= P->maxlev && e == hipSuccess; ++l)
-                e = launch_stage(model, ns, P->kind_mask, P->tile_w, a, P->lev_first[l], P->lev_count[l], s);
+                e = launch_stage(model, ns, P->kind_mask, stage_width(P), a, P->lev_first[l], P->lev_count[l], s);
         } else {
-            e = launch_stage(model, ns, P->kind_mask, P->tile_w, a, 0, a.ntiles, s);
+            e = launch_stage(model, ns, P->kind_mask, stage_width(P), a, 0, a.ntiles, s);
         }
     }
     StageArgs a = base;
@@ -922,7 +933,7 @@ janc_status autotune(janc_ctx* c, janc_plan* P, const janc_time* tm, double* U, 
                 a.Tin = Tin[sg - 1];
                 a.Tout = Tout[sg - 1];
                 a.reduce_out = (sg == 3 && c->model == DETAILED) ? 0 : 1;
-                e = launch_stage(c->model, c->ns, P->kind_mask, P->tile_w, a, 0, a.ntiles, s);
+                e = launch_stage(c->model, c->ns, P->kind_mask, stage_width(P), a, 0, a.ntiles, s);
             }
             if (e == hipSuccess) e = hipEventRecord(ev[1], s);
             if (e == hipSuccess) e = hipEventSynchronize(ev[1]);
@@ -1031,6 +1042,11 @@ janc_status run_steps(janc_ctx* c, janc_plan* P, const janc_time* tm, double* U,
     return JANC_OK;
 }
 
+// A uniform grid whose 32 x 8 tiles are few enough for quarter tiles.
+bool uniform_small(const janc_ctx* c, const janc_grid* g) {
+    return (long long)((g->nx + 31) / 32) * ((g->ny + 7) / 8) <= small_tiles(c->model);
+}
+
 // Plan of a uniform grid: one domain, one level-0 block covering it; cached.
 janc_status uniform_plan(janc_ctx* c, const janc_grid* g, const janc_physics* ph) {
     if (c->uplan && std::memcmp(&c->ugrid, g, sizeof(*g)) == 0 &&
@@ -1046,7 +1062,7 @@ janc_status uniform_plan(janc_ctx* c, const janc_grid* g, const janc_physics* ph
     janc_plan* P = nullptr;
     janc_status st = build_plan(c, 1, &D, 1, &B, (long long)g->nx * g->ny, 0, &P);
     if (st) return st;
-    if (g->ny > 1 && g->nx >= 64 && g->ny < 16) P->tile_w = 64;
+    if (g->ny > 1 && g->nx >= 64 && g->ny < 16 && !uniform_small(c, g)) P->tile_w = 64;
     else if (g->ny > 1 && g->nx >= 32 && g->ny < 32) P->tile_w = 32;
     st = build_tiles(c, P);
     if (st) {
@@ -1127,7 +1143,7 @@ janc_status run_step_noalloc(janc_ctx* c, const janc_grid* g, const janc_physics
         st = build_plan(c, 1, &D, 1, &B, (long long)g->nx * g->ny, JANC_PLAN_NO_GRAPH, &P, base,
                         (size_t)JANC_NOALLOC_SCRATCH_BYTES);
         if (st) return st;
-        if (g->ny > 1 && g->nx >= 64 && g->ny < 16) P->tile_w = 64;
+        if (g->ny > 1 && g->nx >= 64 && g->ny < 16 && !uniform_small(c, g)) P->tile_w = 64;
         else if (g->ny > 1 && g->nx >= 32 && g->ny < 32) P->tile_w = 32;
         st = build_tiles(c, P);
         if (st) {
@@ -1292,7 +1308,7 @@ janc_status run_adjoint(janc_ctx* c, const janc_grid* g, const janc_physics* ph,
         }
         // the detailed model's third stage leaves its maxima to the chemistry step
         a.reduce_out = (det && stn == 3) ? 0 : 1;
-        return launch_stage(model, ns, P->kind_mask, P->tile_w, a, 0, a.ntiles, q);
+        return launch_stage(model, ns, P->kind_mask, stage_width(P), a, 0, a.ntiles, q);
     };
     // the chemistry step of the detailed model: from the third stage's output X into U
     auto chemistry = [&](const double* X, double* U, hipStream_t q) -> hipError_t {
@@ -1892,9 +1908,9 @@ janc_status janc_profile_step(janc_ctx* c, janc_plan* P, const janc_time* tm, do
         a.reduce_out = (st == 3 && model == DETAILED) ? 0 : 1;
         if (P->flags & JANC_PLAN_PER_BLOCK) {
             for (int id = 0; id < P->nblk && e == hipSuccess; ++id)
-                e = launch_stage(model, ns, P->kind_mask, P->tile_w, a, P->tile_first[id], P->tile_count[id], s);
+                e = launch_stage(model, ns, P->kind_mask, stage_width(P), a, P->tile_first[id], P->tile_count[id], s);
         } else {
-            e = launch_stage(model, ns, P->kind_mask, P->tile_w, a, 0, a.ntiles, s);
+            e = launch_stage(model, ns, P->kind_mask, stage_width(P), a, 0, a.ntiles, s);
         }
         if (e == hipSuccess) e = hipEventRecord(ev[st], s);
     }

@@ -113,6 +113,19 @@ __device__ __forceinline__ void publish_max3(const Reduce& r, int buf, int i0, i
     }
 }
 
+// The same for one wave.
+__device__ __forceinline__ void publish_wave3(const Reduce& r, int buf, int i0, int i1, int i2, double v0,
+                                              double v1, double v2) {
+    v0 = wave_max(v0);
+    v1 = wave_max(v1);
+    v2 = wave_max(v2);
+    if ((threadIdx.x & 63) == 0) {
+        if (v0 > 0.0) slot_max(r, buf, i0, v0);
+        if (v1 > 0.0) slot_max(r, buf, i1, v1);
+        if (v2 > 0.0) slot_max(r, buf, i2, v2);
+    }
+}
+
 // The same for values staged in LDS (v[k * 256 + thread], k = 0..2): wave k < 3 takes
 // quantity k of all 256 threads, so that one sixth of the exchanges remain.
 __device__ __forceinline__ void publish_staged(const Reduce& r, int buf, int i0, int i1, int i2,

@@ -156,6 +156,8 @@ hipError_t launch_zero_int(int* p, hipStream_t s);
 hipError_t launch_stage(int model, int ns, int kind_mask, int tile_w, const StageArgs& a,
                         int first_tile, int ntiles, hipStream_t s);
 hipError_t launch_init(int model, int ns, int tile_w, const StageArgs& a, hipStream_t s);
+// Tile width of launch_stage and the halo table that asks for quarter tiles.
+constexpr int QUARTER_TILES = 8;
 // Halo source table (row stride: the largest point count of the tile kinds in kind_mask)
 int halo_table_stride(int tile_w, int kind_mask);
 hipError_t launch_halo_table(int tile_w, const StageArgs& a, int* out, int stride, hipStream_t s);

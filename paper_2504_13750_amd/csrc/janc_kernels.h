@@ -91,12 +91,19 @@ struct Geom {
 // waves left the two of each CU that fit resident, half as many waves as four of four).
 constexpr int STAGE_W = 4;
 constexpr int stage_left(int nu) { return nu % STAGE_W <= 2 ? nu % STAGE_W : 0; }
+// Plans of few tiles cut every tile into four of 64 cells (8 x 8, or 64 of a 1-D block), each
+// swept by one wave per component with one interface per lane: a tile's chain of dependent
+// phases is shorter and four times as many CUs work on it, for 2.5 points fetched and 3
+// interfaces formed per cell and direction pair where whole tiles take 1.75 and 2.25. (9
+// species, 128 x 64 cells: 15.5 -> 10 us per stage.)
+constexpr int SMALL_SPLIT = 4;
 
 // LDS doubles of a stage workgroup: u, v, p (detailed model: times SPLIT_SCALE), source (32
 // bits) and flags (8 bits) of every point, one split-flux buffer per wave.
 template <int TX, int TY>
-constexpr int stage_lds() {
-    return 3 * Geom<TX, TY>::NPP + (5 * Geom<TX, TY>::NPP + 7) / 8 + STAGE_W * Geom<TX, TY>::BUF;
+constexpr int stage_lds(int waves) {
+    return 3 * Geom<TX, TY>::NPP + (5 * Geom<TX, TY>::NPP + 7) / 8 + waves * Geom<TX, TY>::BUF +
+           (Geom<TX, TY>::R == 1 ? 64 : 0);
 }
 
 // Point p of a tile of tw x th valid cells: its tile-local position and whether the x
@@ -153,12 +160,14 @@ __device__ __forceinline__ void split_flux(double u, double v, double al, double
     }
 }
 
-template <int M, int NU, int TX, int TY>
+template <int M, int NU, int TX, int TY, int W>
 __device__ __forceinline__ void stage_tile(const StageArgs& a, const int ti, const Tile tile, double* smem) {
     using G = Geom<TX, TY>;
-    constexpr int R = G::R, NPL = G::NPL, NPP = G::NPP, W = STAGE_W;
-    constexpr int LEFT = stage_left(NU), NR = NU - LEFT;   // components of whole rounds
-    static_assert(R == W && 2 * LEFT <= W, "left-over components: one interface of a run per wave, two buffers each");
+    constexpr int R = G::R, NPL = G::NPL, NPP = G::NPP;
+    constexpr int LEFT = (W < NU) ? stage_left(NU) : 0, NR = NU - LEFT;   // components of whole rounds
+    static_assert(LEFT == 0 || (R == W && 2 * LEFT <= W),
+                  "left-over components: one interface of a run per wave, two buffers each");
+    static_assert(64 * W >= G::NC && (R == 1 || R == W), "phase 2: wave w has cell w of every run");
     constexpr bool DET = M == DETAILED;
     constexpr double scale = DET ? SPLIT_SCALE<M> : 1.0;
     double* pu = smem;                 // u, v, p of every point, times scale
@@ -167,6 +176,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs& a, const int ti, con
     double* bufs = pp + NPP;
     unsigned* psrc = (unsigned*)(bufs + W * G::BUF);
     unsigned char* pfl = (unsigned char*)(psrc + NPP);
+    double* psr = bufs + W * G::BUF + (5 * NPP + 7) / 8;   // (R == 1) explicit source of the cells
 
     // ---------------- phase 0: source and primitives of every point of the tile and its halo
     // Everything a thread loads is on its way before it waits: the table words of its NT
@@ -186,6 +196,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs& a, const int ti, con
     const int bin = (stage == 1 && a.strang) ? 3 : stage - 1, bout = stage % 3;
     const int slot = D.slot0 + lev;
     const int tw = min(TX, B.nx - tile.x0), th = min(TY, B.ny - tile.y0);
+    if (R == 1 && (tw <= 0 || th <= 0)) return;   // a quarter beyond its block's edge
     double ur[NT][NU], Tr[NT];
     unsigned src[NT], pfl0[NT];
 #pragma unroll
@@ -210,7 +221,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs& a, const int ti, con
         if (k == 0) {   // a valid cell of the tile is solved unless it is a ring cell
             int li, lj; // (a coarser source)
             G::point(tid, li, lj);
-            if (needed && li < tw && lj < th && !(fl & 4u)) pfl0[k] |= PT_OWN;
+            if (needed && tid < G::NC && li < tw && lj < th && !(fl & 4u)) pfl0[k] |= PT_OWN;
         }
         const size_t c = s < 0 ? 0 : (size_t)s;
         const double* U = (base ? a.U0 : a.Uin) + c;
@@ -269,6 +280,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs& a, const int ti, con
             if (k == 0) {
                 const double Tc = pr / (ur[k][0] * D.R);
                 src_e = -D.k * ur[k][4] * exp(-D.Ea / Tc);
+                if (LEFT == 0 && tid < G::NC) psr[tid] = src_e;
             }
         }
         pu[p] = scale * vx;
@@ -509,6 +521,10 @@ __device__ __forceinline__ void stage_tile(const StageArgs& a, const int ti, con
             L[q] = -(S[o + 1] - S[o]) * idx;
             if constexpr (G::TWO) L[q] -= (hy[q + 1] - hy[q]) * idy;
         }
+        if constexpr (M == ONESTEP && LEFT == 0) {
+            static_assert(R == 1 || LEFT > 0, "the source is kept for one cell per lane");
+            if (f == 4) L[0] += psr[l];
+        }
         double* out = a.Uout + (size_t)f * a.pool;
 #pragma unroll
         for (int q = 0; q < R; ++q) {
@@ -521,7 +537,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs& a, const int ti, con
 
     // ---------------- phase 2: T, checks, maxima for the next stage
     double sx = 0.0, sy = 0.0, sc = 0.0;
-    if ((own >> w) & 1u) {   // cell tid = 64 w + l
+    if (w < R && ((own >> w) & 1u)) {   // cell tid = 64 w + l
         const long long oc = psrc[tid];
         double unew[NU];
 #pragma unroll
@@ -542,12 +558,16 @@ __device__ __forceinline__ void stage_tile(const StageArgs& a, const int ti, con
             sc = cfl_bound(a, D, lev, sx, sy, idx, idy);
         }
     }
-    if (a.reduce_out) {
+    if (!a.reduce_out) return;
+    const int i0 = 2 * slot, i2 = 2 * a.red.nunits + B.domain;
+    if constexpr (R == 1) {   // one wave holds every cell
+        if (w == 0) publish_wave3(a.red, bout, i0, i0 + 1, i2, sx, sy, sc);
+    } else {
         bufs[tid] = sx;
         bufs[256 + tid] = sy;
         bufs[512 + tid] = sc;
         __syncthreads();
-        publish_staged(a.red, bout, 2 * slot, 2 * slot + 1, 2 * a.red.nunits + B.domain, bufs);
+        publish_staged(a.red, bout, i0, i0 + 1, i2, bufs);
     }
 }
 
@@ -556,18 +576,48 @@ __device__ __forceinline__ void stage_tile(const StageArgs& a, const int ti, con
 #endif
 template <int M, int NU, int TX, int TY, bool HAS1D, bool HAS2D>
 __global__ __launch_bounds__(64 * STAGE_W, STAGE_WAVES) void stage_kernel(StageArgs a, int first_tile, int owner_launch) {
-    constexpr int L2 = HAS2D ? stage_lds<TX, TY>() : 0, L1 = HAS1D ? stage_lds<256, 1>() : 0;
+    constexpr int L2 = HAS2D ? stage_lds<TX, TY>(STAGE_W) : 0, L1 = HAS1D ? stage_lds<256, 1>(STAGE_W) : 0;
     __shared__ __align__(16) double smem[(L2 > L1) ? L2 : L1];
     if (blockIdx.x == 0) stage_bookkeeping(a, owner_launch);
     const int ti = first_tile + (a.linear_sched ? (int)blockIdx.x : xcd_chunk(blockIdx.x, gridDim.x));
     const Tile tile = ctile(a.tiles, ti);
     if (HAS1D && tile.kind == 1) {
-        if constexpr (HAS1D) stage_tile<M, NU, 256, 1>(a, ti, tile, smem);
+        if constexpr (HAS1D) stage_tile<M, NU, 256, 1, STAGE_W>(a, ti, tile, smem);
     } else {
-        if constexpr (HAS2D) stage_tile<M, NU, TX, TY>(a, ti, tile, smem);
+        if constexpr (HAS2D) stage_tile<M, NU, TX, TY, STAGE_W>(a, ti, tile, smem);
     }
     if (a.stage == 3 && (a.cross ? a.xlast : owner_launch) && blockIdx.x == 0) {
         // t and the step counter are read by the next step's first stage only
+        if (M != DETAILED) step_finish(a);
+    }
+}
+
+// Quarter `sub` of a tile.
+__device__ __forceinline__ Tile quarter(Tile t, int sub) {
+    if (t.kind == 1) {
+        t.x0 += 64 * sub;
+    } else {
+        const int n = t.kind >> 11;   // quarters side by side (tile width / 8)
+        t.y0 += 8 * (sub / n);
+        t.x0 += 8 * (sub % n);
+    }
+    return t;
+}
+
+// The stage on quarter tiles: workgroup b takes quarter b % 4 of tile b / 4.
+template <int M, int NU, bool HAS1D, bool HAS2D>
+__global__ __launch_bounds__(64 * NU) void stage_small_kernel(StageArgs a, int first_tile, int owner_launch) {
+    constexpr int L2 = HAS2D ? stage_lds<8, 8>(NU) : 0, L1 = HAS1D ? stage_lds<64, 1>(NU) : 0;
+    __shared__ __align__(16) double smem[(L2 > L1) ? L2 : L1];
+    if (blockIdx.x == 0) stage_bookkeeping(a, owner_launch);
+    const int ti = SMALL_SPLIT * first_tile + (a.linear_sched ? (int)blockIdx.x : xcd_chunk(blockIdx.x, gridDim.x));
+    const Tile tile = quarter(ctile(a.tiles, ti / SMALL_SPLIT), ti % SMALL_SPLIT);
+    if (HAS1D && tile.kind == 1) {
+        if constexpr (HAS1D) stage_tile<M, NU, 64, 1, NU>(a, ti, tile, smem);
+    } else {
+        if constexpr (HAS2D) stage_tile<M, NU, 8, 8, NU>(a, ti, tile, smem);
+    }
+    if (a.stage == 3 && (a.cross ? a.xlast : owner_launch) && blockIdx.x == 0) {
         if (M != DETAILED) step_finish(a);
     }
 }

@@ -79,6 +79,16 @@ def as_blocks(c):
                      W=c.W.reshape(c.nU, -1), mech=c.mech, cfl=c.cfl)
 
 
+@pytest.mark.parametrize("model,nx,ny", [(MODEL_ONESTEP, 129, 131), (MODEL_ONESTEP, 128, 128),
+                                         (MODEL_DETAILED, 128, 128), (MODEL_DETAILED, 145, 128),
+                                         (MODEL_ONESTEP, 16384, 1), (MODEL_ONESTEP, 16385, 1)])
+def test_both_sides_of_the_quarter_tile_rule(model, nx, ny):
+    """64 whole tiles are cut into quarters, 65 and more are not."""
+    c = (detonation_tube_case(nx=nx, ny=ny) if model == MODEL_ONESTEP else
+         detailed_state(9, nx, ny, [BC_ZEROGRAD, BC_DIRICHLET, BC_SLIPWALL, BC_SLIPWALL], inflow=True))
+    check(c, 2)
+
+
 @pytest.mark.parametrize("case", [
     detonation_tube_case(nx=70, ny=13), detonation_tube_case(nx=33, ny=35),
     detailed_state(6, 67, 11, [BC_ZEROGRAD, BC_DIRICHLET, BC_SLIPWALL, BC_SLIPWALL], inflow=True),
