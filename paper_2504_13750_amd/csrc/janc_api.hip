@@ -981,6 +981,59 @@ janc_status autotune(janc_ctx* c, janc_plan* P, const janc_time* tm, double* U, 
     return JANC_OK;
 }
 
+// Whole runs of tiny domains in one launch: every domain 1-D, one block on one level, at most
+// run_cells() cells, a model without chemistry solves, and no flag that asks for a form of
+// its own. Larger domains take one launch per stage.
+bool tiny_domains(const janc_ctx* c, const janc_plan* P) {
+    if (c->model == DETAILED || (P->flags & ~JANC_PLAN_NO_GRAPH) || P->nblk != P->ndom) return false;
+    for (int d = 0; d < P->ndom; ++d) {
+        const DevBlock& b = P->hblk[d];
+        if (b.domain != d || P->hdom[d].nlevels != 1 || P->hdom[d].twod || b.nx > run_cells(c->model))
+            return false;
+    }
+    return true;
+}
+
+// Steps of one launch: the state goes through memory between launches, so the count does
+// not show in the results; it bounds the length of a launch (about 20 ms).
+constexpr int RUN_STEPS = 2048;
+
+janc_status run_tiny(janc_ctx* c, janc_plan* P, const janc_time* tm, double* U, double* T, int nsteps,
+                     double* t, double* dt_log, hipStream_t s) {
+    RunArgs a{};
+    a.U = U;
+    a.T = T;
+    a.t = t;
+    a.pool = P->pool;
+    a.dt_log = dt_log;
+    a.dt_log_cap = nsteps;
+    a.ndom = P->ndom;
+    a.tm = TimeArgs{tm->cfl, tm->dt_fixed, tm->t_end};
+    a.status = c->dstatus;
+    if (P->ndom == 1) {   // by value: nothing to stage for the allocation-free entry point
+        a.dom0 = P->hdom[0];
+        if (P->hblk[0].offset != 0) a.blk = P->dblk;
+    } else {
+        a.dom = P->ddom;
+        a.blk = P->dblk;
+    }
+    if (P->arena) {
+        for (const auto& r : P->dir_rows)
+            for (int q = 0; q < 2; ++q)
+                if (P->hdom[0].dir[q] == r.row) std::memcpy(a.prim[q], r.prim, sizeof(a.prim[q]));
+    } else {
+        a.dirU = P->ddir;
+    }
+    int cells = 0;
+    for (int d = 0; d < P->ndom; ++d) cells = std::max(cells, P->hblk[d].nx);
+    for (int n0 = 0; n0 < nsteps; n0 += RUN_STEPS) {
+        a.step0 = n0;
+        a.nsteps = std::min(RUN_STEPS, nsteps - n0);
+        HIPCHK(c, launch_run(c->model, a, cells, s), "run launch");
+    }
+    return JANC_OK;
+}
+
 // Call entry (T re-solved from U, maxima for the first stage), then nsteps
 // steps: replayed from a captured hipGraph of one step, or launched directly.
 janc_status run_steps(janc_ctx* c, janc_plan* P, const janc_time* tm, double* U, double* T,
@@ -990,6 +1043,7 @@ janc_status run_steps(janc_ctx* c, janc_plan* P, const janc_time* tm, double* U,
         janc_status st = autotune(c, P, tm, U, T, 5, nullptr, s);
         if (st) return st;
     }
+    if (nsteps > 0 && tiny_domains(c, P)) return run_tiny(c, P, tm, U, T, nsteps, t, dt_log, s);
     const StageArgs base = base_args(P, tm, U, T, t, dt_log, nsteps);
     HIPCHK(c, launch_zero_int(P->dstep, s), "counter launch");
     StageArgs a0 = base;
@@ -1154,7 +1208,7 @@ janc_status run_step_noalloc(janc_ctx* c, const janc_grid* g, const janc_physics
         c->ngrid = *g;
         c->nphys = *ph;
     }
-    st = stage_tables(c, c->nplan, s);
+    if (!(nsteps > 0 && tiny_domains(c, c->nplan))) st = stage_tables(c, c->nplan, s);
     if (st) return st;
     return run_steps(c, c->nplan, tm, U, T, nsteps, t, dt_log, s);
 }

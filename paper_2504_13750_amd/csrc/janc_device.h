@@ -79,10 +79,31 @@ __device__ __forceinline__ double uniform(double v) {
     return x.d;
 }
 
+// Value of another lane by a DPP row operation; lanes without a source keep `v`.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp(double v) {
+    union { double d; int i[2]; } x, y;
+    x.d = v;
+    y.i[0] = __builtin_amdgcn_update_dpp(x.i[0], x.i[0], CTRL, ROWS, 0xf, false);
+    y.i[1] = __builtin_amdgcn_update_dpp(x.i[1], x.i[1], CTRL, ROWS, 0xf, false);
+    return y.d;
+}
+
+// Maximum over a wavefront, in every lane: row shifts by 1, 2, 4, 8 leave a row's maximum in
+// its last lane, two broadcasts carry it on to lane 63 (register moves; the exchanges by
+// __shfl_xor went through the LDS pipeline, six dependent trips).
 __device__ __forceinline__ double wave_max(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
-    return v;
+    v = fmax(v, dpp<0x111, 0xf>(v));
+    v = fmax(v, dpp<0x112, 0xf>(v));
+    v = fmax(v, dpp<0x114, 0xf>(v));
+    v = fmax(v, dpp<0x118, 0xf>(v));
+    v = fmax(v, dpp<0x142, 0xa>(v));
+    v = fmax(v, dpp<0x143, 0xc>(v));
+    union { double d; int i[2]; } x;
+    x.d = v;
+    x.i[0] = __builtin_amdgcn_readlane(x.i[0], 63);
+    x.i[1] = __builtin_amdgcn_readlane(x.i[1], 63);
+    return x.d;
 }
 
 // Workgroup max of three values over NW waves; thread 0 publishes them.

@@ -141,6 +141,21 @@ struct StageArgs {
     int hstride;
 };
 
+// A run of tiny domains (run_kernel): one workgroup per domain, all steps in one launch.
+struct RunArgs {
+    const DevDomain* dom;     // [ndom], or null: the one domain dom0
+    const DevBlock* blk;      // [ndom], block d covers domain d; or null: offset 0
+    const double* dirU;       // Dirichlet rows, or null: prim
+    double *U, *T, *t;
+    long long pool;
+    double* dt_log;
+    int dt_log_cap, ndom, nsteps, step0;
+    TimeArgs tm;
+    unsigned* status;
+    DevDomain dom0;
+    double prim[2][5];        // Dirichlet primitives per side
+};
+
 // Layer update: a candidate subregion (layer-`lev` cells) and a fill job.
 struct RegridCand {
     int domain, i0, j0, w, h, pad;
@@ -155,6 +170,10 @@ hipError_t launch_clear_reduce(const Reduce& r, int which, hipStream_t s);
 hipError_t launch_zero_int(int* p, hipStream_t s);
 hipError_t launch_stage(int model, int ns, int kind_mask, int tile_w, const StageArgs& a,
                         int first_tile, int ntiles, hipStream_t s);
+// (1-D domains of the models CPG and ONESTEP; cells: of the largest domain, at most
+// run_cells(model))
+int run_cells(int model);
+hipError_t launch_run(int model, const RunArgs& a, int cells, hipStream_t s);
 hipError_t launch_init(int model, int ns, int tile_w, const StageArgs& a, hipStream_t s);
 // Tile width of launch_stage and the halo table that asks for quarter tiles.
 constexpr int QUARTER_TILES = 8;

@@ -101,6 +101,22 @@ hipError_t launch_halo_table(int tile_w, const StageArgs& a, int* out, int strid
     return hipGetLastError();
 }
 
+// Largest 1-D domain that runs in one workgroup. Measured, us per step of one launch per
+// stage / one run: gas without chemistry 50 cells 22.6 / 8.3, 400 cells 23.9 / 13.4, 1024 cells
+// 24.0 / 20.5; one-step 256 cells 25.4 / 15.5, 700 cells 25.8 / 23.8, 1000 cells 25.8 / 28.4.
+// (Two-dimensional domains were slower from 16 x 16 cells on, 25.3 / 29.8.)
+int run_cells(int model) { return model == CPG ? RUN_CELLS : model == ONESTEP ? 704 : 0; }
+
+hipError_t launch_run(int model, const RunArgs& a, int cells, hipStream_t s) {
+    if (cells < 1 || cells > run_cells(model)) return hipErrorInvalidValue;
+    // whole groups of waves for the interfaces of up to all components
+    const int nu = model == CPG ? 4 : 5, m = (cells + 64) / 64 * 64;
+    const int threads = max((cells + 63) / 64 * 64, m * min(nu, 1024 / m));
+    if (model == CPG) run_kernel<CPG, 4><<<a.ndom, threads, 0, s>>>(a);
+    else run_kernel<ONESTEP, 5><<<a.ndom, threads, 0, s>>>(a);
+    return hipGetLastError();
+}
+
 hipError_t launch_init(int model, int ns, int tile_w, const StageArgs& a, hipStream_t s) {
     (void)tile_w;
     const int n = a.ntiles;
