@@ -350,6 +350,8 @@ janc_status build_plan(janc_ctx* c, int nd, const janc_domain* doms, int nb, con
         }
         h.dx0 = g.dx;
         h.dy0 = g.dy;
+        h.idx0 = 1.0 / g.dx;
+        h.idy0 = 1.0 / g.dy;
         h.gamma = D.phys.gamma;
         h.R = D.phys.R;
         h.Q = D.phys.Q;

@@ -34,6 +34,7 @@ struct DevDomain {
     int slot0;                // alpha slot of level 0 (slot0 + level)
     int cfl_slot;             // index of this domain's CFL slot
     double dx0, dy0;
+    double idx0, idy0;        // 1 / dx0, 1 / dy0
     double gamma, R, Q, Ea, k;
 };
 

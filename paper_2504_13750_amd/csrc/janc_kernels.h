@@ -98,11 +98,11 @@ constexpr int stage_left(int nu) { return nu % STAGE_W <= 2 ? nu % STAGE_W : 0; 
 // species, 128 x 64 cells: 15.5 -> 10 us per stage.)
 constexpr int SMALL_SPLIT = 4;
 
-// LDS doubles of a stage workgroup: u, v, p (detailed model: times SPLIT_SCALE), source (32
-// bits) and flags (8 bits) of every point, one split-flux buffer per wave.
+// LDS doubles of a stage workgroup: u, v, p (detailed model: times SPLIT_SCALE), source and
+// flags (32 bits each) of every point, one split-flux buffer per wave.
 template <int TX, int TY>
 constexpr int stage_lds(int waves) {
-    return 3 * Geom<TX, TY>::NPP + (5 * Geom<TX, TY>::NPP + 7) / 8 + waves * Geom<TX, TY>::BUF +
+    return 3 * Geom<TX, TY>::NPP + Geom<TX, TY>::NPP + waves * Geom<TX, TY>::BUF +
            (Geom<TX, TY>::R == 1 ? 64 : 0);
 }
 
@@ -175,14 +175,15 @@ __device__ __forceinline__ void stage_tile(const StageArgs& a, const int ti, con
     double* pp = pv + NPP;
     double* bufs = pp + NPP;
     unsigned* psrc = (unsigned*)(bufs + W * G::BUF);
-    unsigned char* pfl = (unsigned char*)(psrc + NPP);
-    double* psr = bufs + W * G::BUF + (5 * NPP + 7) / 8;   // (R == 1) explicit source of the cells
+    unsigned* pfl = psrc + NPP;   // flags, and in the high half the place of a halo point in its strip
+    double* psr = bufs + W * G::BUF + NPP;   // (R == 1) explicit source of the cells
 
     // ---------------- phase 0: source and primitives of every point of the tile and its halo
     // Everything a thread loads is on its way before it waits: the table words of its NT
     // points first (they need the tile number alone), then all fields of the points.
     constexpr int NT = (NPP + 64 * W - 1) / (64 * W);
     const int tid = threadIdx.x;
+    __builtin_amdgcn_s_setprio(2);   // loads of a new tile go ahead of the arithmetic of others
     int hv[NT];
 #pragma unroll
     for (int k = 0; k < NT; ++k) {
@@ -242,8 +243,8 @@ __device__ __forceinline__ void stage_tile(const StageArgs& a, const int ti, con
                                                                        : a.dt[B.domain], -lev)
                                       : (stage == 1) ? step_dt(a, B.domain, 0) : a.dt[B.domain]);
     if (!(dt > 0.0)) return;   // finished domain: state unchanged
-    const double dxl = D.dx0 / (double)(1 << lev), dyl = D.dy0 / (double)(1 << lev);
-    const double idx = uniform(1.0 / dxl), idy = uniform(1.0 / dyl);
+    // 1 / (dx0 / 2^lev): scaling by a power of two is exact
+    const double idx = uniform(ldexp(D.idx0, lev)), idy = uniform(ldexp(D.idy0, lev));
     const double ax = uniform(slot_get(a.red, bin, 2 * slot));
     const double ay = uniform(slot_get(a.red, bin, 2 * slot + 1));
     const double sax = uniform(scale * ax), say = uniform(scale * ay);
@@ -287,7 +288,13 @@ __device__ __forceinline__ void stage_tile(const StageArgs& a, const int ti, con
         pv[p] = scale * vy;
         pp[p] = scale * pr;
         psrc[p] = src[k];
-        pfl[p] = (unsigned char)pfl0[k];
+        unsigned place = 0u;
+        if (p >= G::NC) {
+            int li, lj;
+            G::point(p, li, lj);
+            place = (unsigned)(p < G::NC + G::NHX ? lj * G::PX + li + 3 : (lj + 3) * G::PY + li);
+        }
+        pfl[p] = pfl0[k] | place << 16;
     }
     __syncthreads();
 
@@ -309,12 +316,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs& a, const int ti, con
         const unsigned fl = pfl[64 * q + l];
         pf |= (Flags)(fl & 15u) << (4 * q);
         if (q < R) own |= (fl & PT_OWN) ? 1u << q : 0u;
-        hoff[q] = 0;
-        if (q >= R) {
-            int li, lj;
-            G::point(64 * q + l, li, lj);
-            hoff[q] = (64 * q + l < G::NC + G::NHX) ? lj * G::PX + li + 3 : (lj + 3) * G::PY + li;
-        }
+        hoff[q] = (int)(fl >> 16);
     }
     const bool special = __any((pf & (Flags)0xccccccccccccccccull) != 0);
     const int oli = G::TWO ? l % TX : l, olj = G::TWO ? (l / TX) * R : 0;
@@ -386,6 +388,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs& a, const int ti, con
             }
         }
     };
+    __builtin_amdgcn_s_setprio(0);
     double u[NPL], un[NPL];   // this component and, on its way, the wave's next one
     load(w, un);
     for (int f = w; f < NR; f += W) {
@@ -535,13 +538,15 @@ __device__ __forceinline__ void stage_tile(const StageArgs& a, const int ti, con
     }
     __syncthreads();   // the new state of the tile is complete (in the caches)
 
+    __builtin_amdgcn_s_setprio(2);
     // ---------------- phase 2: T, checks, maxima for the next stage
     double sx = 0.0, sy = 0.0, sc = 0.0;
     if (w < R && ((own >> w) & 1u)) {   // cell tid = 64 w + l
         const long long oc = psrc[tid];
+        const double* Uo = a.Uout + oc;
         double unew[NU];
 #pragma unroll
-        for (int f = 0; f < NU; ++f) unew[f] = a.Uout[(size_t)f * a.pool + oc];
+        for (int f = 0; f < NU; ++f) unew[f] = Uo[(size_t)f * a.pool];
         double T, c, vx, vy;
         const unsigned st = owner_state<M, NU>(unew, Town, D, cmech(a.mech), T, c, vx, vy);
         a.Tout[oc] = T;
@@ -690,7 +695,7 @@ __global__ __launch_bounds__(WG) void init_kernel(StageArgs a) {
     CDom& D = cdom(a.dom, B.domain);
     const CellRef r = tile_cell(a, tile, B);
     const int lev = B.level, slot = D.slot0 + lev;
-    const double idx = (double)(1 << lev) / D.dx0, idy = (double)(1 << lev) / D.dy0;
+    const double idx = ldexp(D.idx0, lev), idy = ldexp(D.idy0, lev);
     double sx = 0.0, sy = 0.0, sc = 0.0;
     if (r.own) {
         double u[NU];
@@ -929,7 +934,7 @@ __device__ __forceinline__ void chem_body(const StageArgs& a, double* scratch, C
                                                                    : a.dt[B.domain], -lev)
                                  : (phase == 1) ? step_dt(a, B.domain, 0) : a.dt[B.domain];
     const double dt = (phase == 0) ? dstep : 0.5 * dstep;
-    const double idx = (double)(1 << lev) / D.dx0, idy = (double)(1 << lev) / D.dy0;
+    const double idx = ldexp(D.idx0, lev), idy = ldexp(D.idy0, lev);
     if (blockIdx.x == 0) {
         if (phase == 1) {
             if (!a.cross || a.xfirst) record_dt(a);
@@ -1021,7 +1026,7 @@ __global__ __launch_bounds__(WG) void restrict_kernel(StageArgs a, const int* fi
     const int cw = B.nx / 2, ch = B.ny / 2;
     if (!(dt > 0.0) || (int)blockIdx.y * WG >= cw * ch) return;
     const int cslot = D.slot0 + lev - 1;
-    const double idx = (double)(1 << (lev - 1)) / D.dx0, idy = (double)(1 << (lev - 1)) / D.dy0;
+    const double idx = ldexp(D.idx0, lev - 1), idy = ldexp(D.idy0, lev - 1);
     double sx = 0.0, sy = 0.0, sc = 0.0;
     for (int cc = blockIdx.y * WG + threadIdx.x; cc < cw * ch; cc += gridDim.y * WG) {
         const int cj = cc / cw, ci = cc - cj * cw;
@@ -1180,7 +1185,7 @@ __global__ __launch_bounds__(1024) void run_kernel(RunArgs A) {
     {
         const auto take = [&](const auto& S) {
             D.nx0 = S.nx0;
-            D.dx0 = S.dx0;
+            D.idx0 = S.idx0;
             D.gamma = S.gamma;
             D.R = S.R;
             D.Q = S.Q;
@@ -1202,7 +1207,7 @@ __global__ __launch_bounds__(1024) void run_kernel(RunArgs A) {
     const int m = (n + 64) / 64 * 64, groups = max(1, (int)blockDim.x / m);
     const int g0 = tid / m, k0 = tid - g0 * m;
     const bool ifc = g0 < groups && k0 <= n;
-    const double idx = 1.0 / D.dx0;
+    const double idx = D.idx0;
     if (tid < 2 && bc[tid] == BC_DIRICHLET) {
         double u[NU], vx, vy, pr;
         if (A.dirU) {
