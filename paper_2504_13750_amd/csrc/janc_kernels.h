@@ -721,6 +721,7 @@ template <int NS>
 __device__ __forceinline__ void chem_solve(double (&J)[NS - 1][NS - 1], double (&w)[NS - 1],
                                            double dt, unsigned& st) {
     constexpr int NT = NS - 1;
+    double ipiv[NT];
 #pragma unroll
     for (int k = 0; k < NT; ++k) {
 #pragma unroll
@@ -756,7 +757,8 @@ __device__ __forceinline__ void chem_solve(double (&J)[NS - 1][NS - 1], double (
         }
         const double piv = J[c][c];
         if (!(fabs(piv) > 0.0) || !isfinite(piv)) st |= STB_NONFINITE;
-        const double ip = 1.0 / piv;
+        const double ip = quotient(1.0, piv);
+        ipiv[c] = ip;
 #pragma unroll
         for (int r = c + 1; r < NT; ++r) {
             const double fct = J[r][c] * ip;
@@ -770,7 +772,9 @@ __device__ __forceinline__ void chem_solve(double (&J)[NS - 1][NS - 1], double (
         double sacc = w[r];
 #pragma unroll
         for (int q = r + 1; q < NT; ++q) sacc -= J[r][q] * w[q];
-        w[r] = sacc / J[r][r];
+        // the rounded quotient by the pivot: product with its reciprocal and one residual step
+        const double q0 = sacc * ipiv[r];
+        w[r] = __builtin_fma(__builtin_fma(-J[r][r], q0, sacc), ipiv[r], q0);
     }
 }
 

@@ -7,7 +7,11 @@
 // a loop with wave-uniform branches. With the structure known when the source is
 // compiled, those indices are constants: the same arithmetic, in the same order, runs on
 // registers, and every reaction's rates can be scheduled ahead of the previous one's
-// Jacobian update. The mechanism's numbers become exact hexadecimal literals (no scalar
+// Jacobian update. Terms that the structure makes zero (rates of species that a reaction
+// does not change, derivatives by species that it does not contain) are left out: adding
+// them would not change a bit of a finite sum, but the compiler may not drop them itself.
+// The kernel is bound by its instructions (9 species, 19 reactions, 223 registers, two
+// wavefronts a SIMD: VALU busy 75 %). The mechanism's numbers become exact hexadecimal literals (no scalar
 // loads and waits for them), except the NASA-7 coefficients, whose products with the
 // polynomial's constant factors would otherwise be folded at compile time and round
 // differently from the generic kernel. Only the point-implicit cell step differs; the launch body
@@ -29,12 +33,25 @@ namespace {
 #include "janc_rtc_sources.inc"   // kRtcHeaderNames, kRtcHeaderTexts, kRtcHeaderCount
 
 std::string xs(int j, int ns) { return j >= ns ? std::string("1.0") : "X[" + std::to_string(j) + "]"; }
-std::string gs(int j, int ns) { return j >= ns ? std::string("0.0") : "g[" + std::to_string(j) + "]"; }
+// Sum of the Gibbs terms of a molecule list, in its order, without its padding.
+std::string gsum(const int* l, int ns) {
+    std::string t;
+    for (int q = 0; q < MAXLIST; ++q)
+        if (l[q] < ns) t += (t.empty() ? "g[" : " + g[") + std::to_string(l[q]) + "]";
+    return t.empty() ? "0.0" : t;
+}
 // A number of the mechanism as an exact hexadecimal literal.
 std::string lit(double v) {
     char buf[48];
     std::snprintf(buf, sizeof buf, "(%a)", v);
     return buf;
+}
+// Whether dq/dX_j of reaction i can differ from zero.
+bool depends(const DevMech& d, int i, int j) {
+    if (d.has_tb[i]) return true;
+    for (int q = 0; q < MAXLIST; ++q)
+        if (d.lf[i][q] == j || d.lb[i][q] == j) return true;
+    return false;
 }
 }  // namespace
 
@@ -54,7 +71,8 @@ std::string chem_spec_source(const DevMech& d) {
     // polynomial's constant factors would be folded at compile time (rounded once, where
     // the generic kernel fuses them into the next multiply-add)
     o << "    double g[" << ns << "];\n#pragma unroll\n    for (int j = 0; j < " << ns << "; ++j) {\n"
-         "        const bool hi = m->two_range && T >= m->tmid[j];\n        double a[7];\n#pragma unroll\n"
+      << (d.two_range ? "        const bool hi = T >= m->tmid[j];\n" : "        const bool hi = false;\n") <<
+         "        double a[7];\n#pragma unroll\n"
          "        for (int q = 0; q < 7; ++q) a[q] = hi ? m->nasa_hi[j][q] : m->nasa[j][q];\n"
          "        g[j] = a[0] * (1.0 - lnT) -\n"
          "               T * (0.5 * a[1] + T * (a[2] * (1.0 / 6.0) + T * (a[3] * (1.0 / 12.0) + T * (a[4] * 0.05)))) +\n"
@@ -69,9 +87,10 @@ std::string chem_spec_source(const DevMech& d) {
         o << "        const double lnkf = " << lit(d.lnA[i]) << " + " << lit(d.b[i]) << " * lnT - " << lit(d.EaR[i]) << " * invT;\n";
         o << "        const double kf = exp(lnkf);\n";
         if (d.rev[i]) {
-            o << "        const double sg = (" << gs(b[0], ns) << " + " << gs(b[1], ns) << " + " << gs(b[2], ns) << ") - ("
-              << gs(f[0], ns) << " + " << gs(f[1], ns) << " + " << gs(f[2], ns) << ");\n";
-            o << "        const double kb = exp(lnkf + sg - " << lit((double)d.dnsum[i]) << " * lnC);\n";
+            o << "        const double sg = (" << gsum(b, ns) << ") - (" << gsum(f, ns) << ");\n";
+            o << "        const double kb = exp(lnkf + sg";
+            if (d.dnsum[i] != 0) o << " - " << lit((double)d.dnsum[i]) << " * lnC";
+            o << ");\n";
         } else {
             o << "        const double kb = 0.0;\n";
         }
@@ -85,7 +104,8 @@ std::string chem_spec_source(const DevMech& d) {
             o << "        const double ctb = 1.0;\n";
         }
         o << "        const double net = Rf - Rb;\n        const double q = ctb * net;\n";
-        for (int k = 0; k < nt; ++k) o << "        w[" << k << "] += " << lit(d.Mdnu[i][k]) << " * q;\n";
+        for (int k = 0; k < nt; ++k)
+            if (d.Mdnu[i][k] != 0.0) o << "        w[" << k << "] += " << lit(d.Mdnu[i][k]) << " * q;\n";
         o << "        double dq[" << ns + 1 << "];\n";
         for (int j = 0; j <= ns; ++j) {
             o << "        dq[" << j << "] = ";
@@ -99,13 +119,19 @@ std::string chem_spec_source(const DevMech& d) {
         o << "        dq[" << b[0] << "] -= cb * (xb1 * xb2);\n";
         o << "        dq[" << b[1] << "] -= cb * (xb0 * xb2);\n";
         o << "        dq[" << b[2] << "] -= cb * (xb0 * xb1);\n";
-        o << "        const double dlast = dq[" << nt << "] * " << lit(d.invM[nt]) << ";\n";
-        o << "        double Dm[" << nt << "];\n";
-        for (int mm = 0; mm < nt; ++mm) o << "        Dm[" << mm << "] = dq[" << mm << "] * " << lit(d.invM[mm]) << " - dlast;\n";
+        const bool last = depends(d, i, nt);
+        if (last) o << "        const double dlast = dq[" << nt << "] * " << lit(d.invM[nt]) << ";\n";
+        for (int mm = 0; mm < nt; ++mm) {
+            if (!last && !depends(d, i, mm)) continue;
+            o << "        const double D" << mm << " = ";
+            if (depends(d, i, mm)) o << "dq[" << mm << "] * " << lit(d.invM[mm]) << (last ? " - dlast;\n" : ";\n");
+            else o << "-dlast;\n";
+        }
         for (int k = 0; k < nt; ++k) {
             if (d.dnu[i][k] == 0) continue;
             for (int mm = 0; mm < nt; ++mm)
-                o << "        J[" << k << "][" << mm << "] += " << lit(d.Mdnu[i][k]) << " * Dm[" << mm << "];\n";
+                if (last || depends(d, i, mm))
+                    o << "        J[" << k << "][" << mm << "] += " << lit(d.Mdnu[i][k]) << " * D" << mm << ";\n";
         }
         o << "    }\n";
     }
@@ -150,7 +176,8 @@ std::string adj_chem_spec_source(const DevMech& d) {
             o << "            const double ctb = 1.0;\n";
         }
         o << "            const double q = ctb * (Rf - Rb);\n";
-        for (int k = 0; k < nt; ++k) o << "            S[" << k << "] += " << lit(d.Mdnu[i][k]) << " * q;\n";
+        for (int k = 0; k < nt; ++k)
+            if (d.Mdnu[i][k] != 0.0) o << "            S[" << k << "] += " << lit(d.Mdnu[i][k]) << " * q;\n";
         o << "            double dq[" << ns + 1 << "];\n";
         for (int j = 0; j <= ns; ++j) {
             if (d.has_tb[i] && j < ns) o << "            dq[" << j << "] = " << lit(d.tb[i][j]) << " * (Rf - Rb);\n";
@@ -162,12 +189,16 @@ std::string adj_chem_spec_source(const DevMech& d) {
         o << "            dq[" << b[0] << "] -= ctb * kb * (X[" << b[1] << "] * X[" << b[2] << "]);\n";
         o << "            dq[" << b[1] << "] -= ctb * kb * (X[" << b[0] << "] * X[" << b[2] << "]);\n";
         o << "            dq[" << b[2] << "] -= ctb * kb * (X[" << b[0] << "] * X[" << b[1] << "]);\n";
-        o << "            const double dl = dq[" << nt << "] * " << lit(d.invM[nt]) << ";\n";
+        const bool last = depends(d, i, nt);
+        if (last) o << "            const double dl = dq[" << nt << "] * " << lit(d.invM[nt]) << ";\n";
         for (int k = 0; k < nt; ++k) {
             if (d.dnu[i][k] == 0) continue;
-            for (int q2 = 0; q2 < nt; ++q2)
-                o << "            J[" << k << "][" << q2 << "] += " << lit(d.Mdnu[i][k]) << " * (dq[" << q2
-                  << "] * " << lit(d.invM[q2]) << " - dl);\n";
+            for (int q2 = 0; q2 < nt; ++q2) {
+                if (!last && !depends(d, i, q2)) continue;
+                o << "            J[" << k << "][" << q2 << "] += " << lit(d.Mdnu[i][k]) << " * ";
+                if (depends(d, i, q2)) o << "(dq[" << q2 << "] * " << lit(d.invM[q2]) << (last ? " - dl);\n" : ");\n");
+                else o << "-dl;\n";
+            }
         }
         o << "        }\n";
     }
@@ -182,7 +213,8 @@ std::string adj_chem_spec_source(const DevMech& d) {
         const int* b = d.lb[i];
         const std::string I = std::to_string(i);
         o << "        {  // reaction " << i << "\n            double ci = 0.0;\n";
-        for (int k = 0; k < nt; ++k) o << "            ci += mu[" << k << "] * " << lit(d.Mdnu[i][k]) << ";\n";
+        for (int k = 0; k < nt; ++k)
+            if (d.Mdnu[i][k] != 0.0) o << "            ci += mu[" << k << "] * " << lit(d.Mdnu[i][k]) << ";\n";
         o << "            if (ci != 0.0) {\n";
         o << "                const double lnkf = " << lit(d.lnA[i]) << " + " << lit(d.b[i]) << " * lnT - " << lit(d.EaR[i]) << " * invT;\n";
         o << "                const double kf = exp(lnkf);\n                double kb = 0.0, dlb = 0.0;\n";
