@@ -10,7 +10,7 @@ point-implicit chemistry, synchronous advance with restriction; FP64.
 Metric: FP64 cell-stage updates/s = (cells of valid blocks, ring cells included)
 x 3 RK stages x steps / wall time of the timed region, inputs resident in HBM.
 Reported beside it: the same update in the per-block launch form (one launch per
-block and stage, no graph), the stage kernel's roofline position (FP64 VALU bound)
+block and stage), the stage kernel's roofline position (FP64 VALU bound)
 from HIP events, and the CPU oracle on a bounded sample.
 
 python bench.py [--gpus 1] [--steps K] [--warmup W]
@@ -322,20 +322,19 @@ def main():
                      "ms_per_step": 1e3 * pb_s / args.per_block_steps,
                      "steps": args.per_block_steps,
                      "speedup_of_fused": value / pb_value,
-                     "form": "one launch per block and RK stage, no graph"}
+                     "form": "one launch per block and RK stage"}
         log(f"[bench] per-block form {per_block['ms_per_step']:.3f} ms/step "
             f"-> fused speed-up {value / pb_value:.2f}x")
         pplan.close()
         # the paper's structure: one batched launch per refinement level and stage
-        # (graph-captured like the fused form)
         lplan = ctx.plan(domains, case.blocks, case.pool_cells, janc.PLAN_PER_LEVEL)
         pl_s, _, _ = timed_run(lplan, args.steps, args.warmup)
         pl_value = cells * 3 * args.steps / pl_s
         per_block["per_level"] = {"value": pl_value, "unit": "cell-stage/s",
                                   "ms_per_step": 1e3 * pl_s / args.steps, "steps": args.steps,
                                   "speedup_of_fused": value / pl_value,
-                                  "form": "one launch per refinement level and RK stage, "
-                                          "graph-captured (per-level batching, Alg. 2)"}
+                                  "form": "one launch per refinement level and RK stage "
+                                          "(per-level batching, Alg. 2)"}
         log(f"[bench] per-level form {per_block['per_level']['ms_per_step']:.3f} ms/step "
             f"-> fused speed-up {value / pl_value:.2f}x")
         lplan.close()
@@ -511,7 +510,7 @@ def main():
             return e0.elapsed_time(e1) / 1e3, out
 
         fwd()
-        adj()                      # warm-up (workspace, graph capture)
+        adj()                      # warm-up (workspace)
         tf = min(fwd() for _ in range(3))
         ta = min(adj()[0] for _ in range(3))
         actx.sync_status()

@@ -189,7 +189,7 @@ janc_status janc_step(janc_ctx *ctx, const janc_grid *grid, const janc_physics *
  * states, reductions and plan tables live in the static array above: a grid needs about
  * 16 (nfields + 1) bytes per cell plus small tables (9 species: about 320 k cells; the
  * one-step model: about 690 k cells); larger grids are rejected with JANC_EINVAL and a
- * message, before any device work. The steps are launched directly (no graph); the tables
+ * message, before any device work. The steps are launched directly; the tables
  * are copied into the array on `stream` at every call. Every call on a device shares that
  * device's array, which keeps the last call's contents: calls that overlap on one device
  * (other streams, other threads, other contexts) race and must be serialized by the
@@ -224,7 +224,7 @@ typedef struct janc_plan janc_plan;
 enum {
     JANC_PLAN_DEFAULT = 0,
     JANC_PLAN_PER_BLOCK = 1,   /* one launch per block and stage (comparison form) */
-    JANC_PLAN_NO_GRAPH = 2,    /* launch kernels directly instead of a captured hipGraph */
+    JANC_PLAN_NO_GRAPH = 2,    /* accepted; every plan launches its kernels directly */
     JANC_PLAN_CROSSOVER = 4,   /* crossover advance (Fig. 2a, Alg. 2) instead of the synchronous one */
     JANC_PLAN_PER_LEVEL = 8,   /* one stage launch per refinement level (comparison form: the
                                   paper's per-level batching of equal-shape blocks, Alg. 2) */
@@ -333,7 +333,7 @@ janc_status janc_regrid_fill(janc_ctx *ctx, janc_plan *old_plan, const double *U
                              double *T_new, void *stream);
 
 /* Profiling aid: one step of a plan (as in janc_step_blocks, after the call-entry
- * temperature solve) launched without graph capture, with HIP events recorded on
+ * temperature solve) launched with HIP events recorded on
  * `stream` around each launch group. ms (host) [6] receives the durations in
  * milliseconds of RK stage 1, stage 2, stage 3, the chemistry step, the
  * restriction (all levels) and the ring refill. U_pool, T_pool and t advance by

@@ -1,6 +1,6 @@
 // janc_api.hip -- host runtime behind the C ABI of include/janc.h: contexts,
 // block-table plans (validation, level maps, coarse-fine ring masks, tiles,
-// restriction lists), call sequencing and hipGraph capture of whole steps.
+// restriction lists), call sequencing.
 #include <algorithm>
 #include <cmath>
 #include <cstdarg>
@@ -64,19 +64,6 @@ struct janc_ctx {
     std::string adj_chem_log;
 };
 
-struct GraphKey {
-    const double *U, *T, *t, *dt_log;
-    int cap;
-    double cfl, dt_fixed, t_end;
-    int split, jac;
-    int chem;   // the context's chemistry kernel (generic or specialised)
-    bool operator==(const GraphKey& o) const {
-        return U == o.U && T == o.T && t == o.t && dt_log == o.dt_log && cap == o.cap &&
-               cfl == o.cfl && dt_fixed == o.dt_fixed && t_end == o.t_end && split == o.split &&
-               jac == o.jac && chem == o.chem;
-    }
-};
-
 struct janc_plan {
     janc_ctx* ctx = nullptr;
     int flags = 0;
@@ -115,12 +102,6 @@ struct janc_plan {
     std::vector<int> fine_off, fine_flat;
     int* dring = nullptr;
     double *U1 = nullptr, *U2 = nullptr, *T1 = nullptr, *T2 = nullptr;
-    // graph cache
-    bool have_graph = false;
-    GraphKey gkey{};
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t gexec = nullptr;
-    hipEvent_t gdone = nullptr;    // recorded after the last replay of the graph
     // Workspace source. arena == nullptr: every device array is a hipMalloc of its own.
     // Otherwise arrays are carved from [arena, arena + arena_cap) (the static scratch
     // array of janc_step_noalloc) and nothing is copied at build time: the host tables
@@ -189,10 +170,6 @@ template <class T> janc_status upload(janc_ctx* c, T** p, const std::vector<T>& 
 
 void plan_free(janc_plan* p) {
     if (!p) return;
-    if (p->gdone) hipEventSynchronize(p->gdone);
-    if (p->gexec) hipGraphExecDestroy(p->gexec);
-    if (p->graph) hipGraphDestroy(p->graph);
-    if (p->gdone) hipEventDestroy(p->gdone);
     if (!p->arena) {
         void* ptrs[] = {p->ddom, p->dblk, p->dmap, p->dtiles, p->dhsrc, p->ddir, p->dred, p->ddt,
                         p->dstep, p->dfine, p->dring, p->U1, p->U2, p->T1, p->T2};
@@ -850,17 +827,6 @@ hipError_t enqueue_step(janc_plan* P, const StageArgs& base, double* U, double* 
     return e;
 }
 
-// The executable graph may still be replaying on the stream of an earlier call:
-// wait for its last replay before destroying it.
-void drop_graph(janc_plan* P) {
-    if (P->gexec && P->gdone) hipEventSynchronize(P->gdone);
-    if (P->gexec) hipGraphExecDestroy(P->gexec);
-    if (P->graph) hipGraphDestroy(P->graph);
-    P->gexec = nullptr;
-    P->graph = nullptr;
-    P->have_graph = false;
-}
-
 // Autotuner of the stage launch. Candidates: the 2-D tile width 16, 32 or 64 (16 x 16,
 // 32 x 8, 64 x 4 cells) times the order in which workgroups take tiles. A measurement
 // is one RK stage triple of the plan on the state (U, T), timed with HIP events: stage
@@ -976,7 +942,6 @@ janc_status autotune(janc_ctx* c, janc_plan* P, const janc_time* tm, double* U, 
         janc_status st2 = build_tiles(c, P);
         if (!st) st = st2;
     }
-    drop_graph(P);
     if (e != hipSuccess) return hipfail(c, e, "autotune");
     if (st) return st;
     P->tuned = true;
@@ -1037,7 +1002,12 @@ janc_status run_tiny(janc_ctx* c, janc_plan* P, const janc_time* tm, double* U, 
 }
 
 // Call entry (T re-solved from U, maxima for the first stage), then nsteps
-// steps: replayed from a captured hipGraph of one step, or launched directly.
+// steps, every kernel launched directly: also the shortest steps measured (20 us, three
+// launches) keep the host ahead of the device. Replaying a captured graph of one step left
+// the device idle for about 4 us between replays: one-step 1024 x 128 cells 54.5 -> 49.3 us
+// per step, 9 species 512 x 256 97 -> 94 us, 64 x 64 cells without a source term 25.0 -> 22.0
+// us; no plan measured, from 16 x 16 cells to 4 M, was faster replayed. A graph of five steps
+// was within 4 % of this either way, and costs its capture on every new buffer.
 janc_status run_steps(janc_ctx* c, janc_plan* P, const janc_time* tm, double* U, double* T,
                       int nsteps, double* t, double* dt_log, hipStream_t s) {
     HIPCHK(c, hipSetDevice(c->device), "hipSetDevice");
@@ -1066,35 +1036,7 @@ janc_status run_steps(janc_ctx* c, janc_plan* P, const janc_time* tm, double* U,
         }
     }
     if (nsteps == 0) return JANC_OK;
-    if (P->flags & JANC_PLAN_NO_GRAPH) {
-        for (int n = 0; n < nsteps; ++n) HIPCHK(c, enqueue_step(P, base, U, T, s), "step launch");
-        return JANC_OK;
-    }
-    // the step count enters the captured launches only as the bound of dt_log
-    const GraphKey key{U, T, t, dt_log, dt_log ? nsteps : 0, tm->cfl, tm->dt_fixed, tm->t_end,
-                       tm->split, tm->jac, c->chem_mode};
-    if (!P->have_graph || !(P->gkey == key)) {
-        drop_graph(P);
-        hipStream_t cs;
-        HIPCHK(c, hipStreamCreateWithFlags(&cs, hipStreamNonBlocking), "capture stream");
-        hipError_t e = hipStreamBeginCapture(cs, hipStreamCaptureModeRelaxed);
-        if (e == hipSuccess) {
-            hipError_t e2 = enqueue_step(P, base, U, T, cs);
-            e = hipStreamEndCapture(cs, &P->graph);
-            if (e2 != hipSuccess) e = e2;
-        }
-        if (e == hipSuccess) e = hipGraphInstantiate(&P->gexec, P->graph, nullptr, nullptr, 0);
-        hipStreamDestroy(cs);
-        if (e != hipSuccess) {
-            drop_graph(P);
-            return hipfail(c, e, "graph capture");
-        }
-        P->gkey = key;
-        P->have_graph = true;
-    }
-    for (int n = 0; n < nsteps; ++n) HIPCHK(c, hipGraphLaunch(P->gexec, s), "hipGraphLaunch");
-    if (!P->gdone) HIPCHK(c, hipEventCreateWithFlags(&P->gdone, hipEventDisableTiming), "hipEventCreate");
-    HIPCHK(c, hipEventRecord(P->gdone, s), "hipEventRecord");
+    for (int n = 0; n < nsteps; ++n) HIPCHK(c, enqueue_step(P, base, U, T, s), "step launch");
     return JANC_OK;
 }
 
@@ -1178,7 +1120,7 @@ janc_status stage_tables(janc_ctx* c, janc_plan* P, hipStream_t s) {
 
 // janc_step with every workspace in the static scratch array: the uniform plan's host
 // tables are built (and cached) on the host, their device arrays are pieces of the
-// scratch array, and the steps are launched directly (no graph).
+// scratch array, and the steps are launched.
 janc_status run_step_noalloc(janc_ctx* c, const janc_grid* g, const janc_physics* ph,
                              const janc_time* tm, double* U, double* T, int nsteps, double* t,
                              double* dt_log, hipStream_t s) {
@@ -1876,7 +1818,6 @@ janc_status janc_plan_set_tile(janc_plan* p, int w) {
     if (w == 0) w = 16;
     if (w != 16 && w != 32 && w != 64) return fail(p->ctx, JANC_EINVAL, "tile width must be 16, 32 or 64");
     p->tile_w = w;
-    drop_graph(p);
     return build_tiles(p->ctx, p);
 }
 
@@ -1899,7 +1840,6 @@ janc_status janc_plan_set_schedule(janc_plan* p, int tile_w, int linear) {
     if (!p) return JANC_EINVAL;
     if (linear != 0 && linear != 1) return fail(p->ctx, JANC_EINVAL, "linear must be 0 or 1");
     p->linear_sched = linear;
-    drop_graph(p);
     return janc_plan_set_tile(p, tile_w);
 }
 
