@@ -689,31 +689,49 @@ __device__ __forceinline__ CellRef tile_cell(const StageArgs& a, const Tile& til
 }
 
 // Call entry: T re-solved from U (warm start = stored T) and the maxima for stage 1.
+//
+// A workgroup takes `per` tiles in turn and publishes when the slots change: one address takes
+// an atomic every 13 ns, and three per tile were the length of this launch at many tiles (9
+// species, everything before the first step: 7,750 tiles 256 -> 190 us, 15,750 tiles 326 ->
+// 187 us). Below INIT_MANY tiles the launch is short and one each fills the chip better.
+constexpr int INIT_MANY = 4096, INIT_PER = 4;
+inline int init_per(int ntiles) { return ntiles >= INIT_MANY ? INIT_PER : 1; }
 template <int M, int NU>
-__global__ __launch_bounds__(WG) void init_kernel(StageArgs a) {
+__global__ __launch_bounds__(WG) void init_kernel(StageArgs a, int per) {
     __shared__ double scratch[16];
-    const Tile tile = a.tiles[blockIdx.x];
-    const DevBlock B = a.blk[tile.block];
-    CDom& D = cdom(a.dom, B.domain);
-    const CellRef r = tile_cell(a, tile, B);
-    const int lev = B.level, slot = D.slot0 + lev;
-    const double idx = ldexp(D.idx0, lev), idy = ldexp(D.idy0, lev);
     double sx = 0.0, sy = 0.0, sc = 0.0;
-    if (r.own) {
-        double u[NU];
+    const int t0 = blockIdx.x * per, t1 = min(t0 + per, a.ntiles);
+    for (int ti = t0; ti < t1; ++ti) {
+        const Tile tile = a.tiles[ti];
+        const DevBlock B = a.blk[tile.block];
+        CDom& D = cdom(a.dom, B.domain);
+        const CellRef r = tile_cell(a, tile, B);
+        const int lev = B.level, slot = D.slot0 + lev;
+        const double idx = ldexp(D.idx0, lev), idy = ldexp(D.idy0, lev);
+        if (r.own) {
+            double u[NU];
 #pragma unroll
-        for (int f = 0; f < NU; ++f) u[f] = a.Uin[(size_t)f * a.pool + r.c];
-        double T, c, vx, vy;
-        const unsigned st = owner_state<M, NU>(u, a.Tin[r.c], D, cmech(a.mech), T, c, vx, vy);
-        a.Tout[r.c] = T;
-        if (st) atomicOr(a.status, st);
-        else {
-            sx = fabs(vx) + c;
-            sy = fabs(vy) + c;
-            sc = cfl_bound(a, D, lev, sx, sy, idx, idy);
+            for (int f = 0; f < NU; ++f) u[f] = a.Uin[(size_t)f * a.pool + r.c];
+            double T, c, vx, vy;
+            const unsigned st = owner_state<M, NU>(u, a.Tin[r.c], D, cmech(a.mech), T, c, vx, vy);
+            a.Tout[r.c] = T;
+            if (st) atomicOr(a.status, st);
+            else {
+                sx = fmax(sx, fabs(vx) + c);
+                sy = fmax(sy, fabs(vy) + c);
+                sc = fmax(sc, cfl_bound(a, D, lev, fabs(vx) + c, fabs(vy) + c, idx, idy));
+            }
+        }
+        bool last = ti + 1 == t1;
+        if (!last) {
+            const DevBlock N = a.blk[a.tiles[ti + 1].block];
+            last = N.level != lev || N.domain != B.domain;
+        }
+        if (last) {
+            publish_max3<WG / 64>(a.red, 0, 2 * slot, 2 * slot + 1, 2 * a.red.nunits + B.domain, sx, sy, sc, scratch);
+            sx = sy = sc = 0.0;
         }
     }
-    publish_max3<WG / 64>(a.red, 0, 2 * slot, 2 * slot + 1, 2 * a.red.nunits + B.domain, sx, sy, sc, scratch);
 }
 
 // (I - dt J) dU = dt w of the point-implicit step (Eq. 4.12-4.13) for the Jacobian J of

@@ -119,10 +119,10 @@ hipError_t launch_run(int model, const RunArgs& a, int cells, hipStream_t s) {
 
 hipError_t launch_init(int model, int ns, int tile_w, const StageArgs& a, hipStream_t s) {
     (void)tile_w;
-    const int n = a.ntiles;
-    if (n <= 0) return hipSuccess;
-    if (model == CPG) init_kernel<CPG, 4><<<n, WG, 0, s>>>(a);
-    else if (model == ONESTEP) init_kernel<ONESTEP, 5><<<n, WG, 0, s>>>(a);
+    if (a.ntiles <= 0) return hipSuccess;
+    const int per = init_per(a.ntiles), n = (a.ntiles + per - 1) / per;
+    if (model == CPG) init_kernel<CPG, 4><<<n, WG, 0, s>>>(a, per);
+    else if (model == ONESTEP) init_kernel<ONESTEP, 5><<<n, WG, 0, s>>>(a, per);
     else {
         const SpeciesOps* o = species_ops(ns);
         return o ? o->init(a, s) : hipErrorInvalidValue;

@@ -22,7 +22,8 @@ hipError_t stage(int kind_mask, int tile_w, const StageArgs& a, int first, int n
 }
 
 hipError_t init(const StageArgs& a, hipStream_t s) {
-    init_kernel<DETAILED, NU><<<a.ntiles, WG, 0, s>>>(a);
+    const int per = init_per(a.ntiles);
+    init_kernel<DETAILED, NU><<<(a.ntiles + per - 1) / per, WG, 0, s>>>(a, per);
     return hipGetLastError();
 }
 
