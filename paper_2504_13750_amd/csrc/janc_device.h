@@ -423,16 +423,26 @@ __device__ __forceinline__ double weno5(double a, double b, double c, double d, 
 template <int M>
 constexpr double SPLIT_SCALE = (M == DETAILED) ? 1.0 / 12.0 : 0.5;
 
+// weno5_flux of the detailed model divides by the product of two sums of squared smoothness
+// indicators, the sixteenth power of a flux difference: in range while the split fluxes stay
+// below 2^59 (5.8e17) in magnitude, for every shape of a stencil. The reconstruction is
+// homogeneous, so tiles beyond that are reconstructed at WENO_SHRINK times their fluxes, which
+// holds to differences of 2e33, as far as a division for each side alone did (1.6e33). The
+// smallest denominator, of equal fluxes, is 2^-994 then; the numerator above it is exact to
+// 2^-1074, 2e-9 of a flux.
+constexpr double WENO_C1 = 12.0 * WENO_EPS / 108.0, WENO_SHRINK = 0x1p-51;
+
 // One-sided WENO5-JS from a..e (a sixth of the split fluxes) as c + num / den: weno5()'s
 // form with everything over 36 * 3 in the smoothness indicators (their common factor
-// cancels in the weights) and the linear weights 1 : 6 : 3.
+// cancels in the weights) and the linear weights 1 : 6 : 3. c1: WENO_C1, or for fluxes
+// multiplied by WENO_SHRINK its square times that.
 __device__ __forceinline__ void weno5_parts(double a, double b, double c, double d, double e,
-                                            double& num, double& den) {
-    constexpr double C1 = 12.0 * WENO_EPS / 108.0, C2 = 13.0 / 3.0;
+                                            double& num, double& den, double c1) {
+    constexpr double C2 = 13.0 / 3.0;
     const double d1 = b - a, d2 = c - b, d3 = d - c, d4 = e - d;
     const double t0 = d2 - d1, t1 = d3 - d2, t2 = d4 - d3;
     const double u0 = 3.0 * d2 - d1, u1 = d2 + d3, u2 = 3.0 * d3 - d4;
-    const double b0 = C1 + (C2 * t0) * t0, b1 = C1 + (C2 * t1) * t1, b2 = C1 + (C2 * t2) * t2;
+    const double b0 = c1 + (C2 * t0) * t0, b1 = c1 + (C2 * t1) * t1, b2 = c1 + (C2 * t2) * t2;
     const double s0 = sq(b0 + u0 * u0), s1 = sq(b1 + u1 * u1), s2 = sq(b2 + u2 * u2);
     const double w0 = s1 * s2, w1 = 6.0 * (s0 * s2), w2 = 3.0 * (s0 * s1);
     const double r0 = 2.0 * u0 - d2, r1 = u1 + d3, r2 = d3 + u2;
@@ -444,12 +454,13 @@ __device__ __forceinline__ void weno5_parts(double a, double b, double c, double
 // (its stencil mirrored). The detailed model takes both over one denominator.
 template <int M>
 __device__ __forceinline__ double weno5_flux(double p0, double p1, double p2, double p3, double p4,
-                                             double& m0, double m1, double m2, double m3, double m4) {
+                                             double& m0, double m1, double m2, double m3, double m4,
+                                             double c1) {
     if constexpr (M == DETAILED) {
         double np, dp, nm, dm;
-        weno5_parts(p0, p1, p2, p3, p4, np, dp);
+        weno5_parts(p0, p1, p2, p3, p4, np, dp, c1);
         after(dp, m0);
-        weno5_parts(m0, m1, m2, m3, m4, nm, dm);
+        weno5_parts(m0, m1, m2, m3, m4, nm, dm, c1);
         const double q = quotient(np * dm + nm * dp, dp * dm);
         return 6.0 * (p2 + m2) + q;
     } else {
@@ -460,8 +471,8 @@ __device__ __forceinline__ double weno5_flux(double p0, double p1, double p2, do
 }
 
 template <int M>
-__device__ __forceinline__ double weno5_pair(const double (&P)[5], double (&N)[5]) {
-    return weno5_flux<M>(P[0], P[1], P[2], P[3], P[4], N[0], N[1], N[2], N[3], N[4]);
+__device__ __forceinline__ double weno5_pair(const double (&P)[5], double (&N)[5], double c1) {
+    return weno5_flux<M>(P[0], P[1], P[2], P[3], P[4], N[0], N[1], N[2], N[3], N[4], c1);
 }
 
 // R consecutive interfaces from LDS strips of stride STR: F+ from p[k .. k+4], F- from
@@ -469,7 +480,7 @@ __device__ __forceinline__ double weno5_pair(const double (&P)[5], double (&N)[5
 // squares. The strips are read as the run advances and the interfaces kept in order, so
 // that one interface's working set is live at a time (all R at once took 60 more registers).
 template <int M, int R, int STR>
-__device__ __forceinline__ void weno5_runs(const double* p, const double* n, double (&h)[R]) {
+__device__ __forceinline__ void weno5_runs(const double* p, const double* n, double (&h)[R], double c1) {
     double P[R + 4], N[R + 4];
 #pragma unroll
     for (int k = 0; k < 5; ++k) {
@@ -483,9 +494,45 @@ __device__ __forceinline__ void weno5_runs(const double* p, const double* n, dou
             N[k + 5] = n[(k + 5) * STR];
         }
         h[k] = weno5_flux<M>(P[k], P[k + 1], P[k + 2], P[k + 3], P[k + 4],
-                             N[k + 4], N[k + 3], N[k + 2], N[k + 1], N[k]);
+                             N[k + 4], N[k + 3], N[k + 2], N[k + 1], N[k], c1);
         if (k + 1 < R) after(h[k], P[k + 5]);
     }
+}
+
+// One interface; `wide` (the same in every lane): at WENO_SHRINK times its fluxes.
+template <int M, int STR>
+__device__ __forceinline__ double weno5_one(const double* p, const double* n, bool wide) {
+    double P[5], N[5];
+#pragma unroll
+    for (int k = 0; k < 5; ++k) {
+        P[k] = p[k * STR];
+        N[k] = n[(4 - k) * STR];
+    }
+    if (M == DETAILED && __builtin_expect(wide, 0)) {
+#pragma unroll
+        for (int k = 0; k < 5; ++k) {
+            P[k] *= WENO_SHRINK;
+            N[k] *= WENO_SHRINK;
+        }
+        return weno5_pair<M>(P, N, WENO_C1 * WENO_SHRINK * WENO_SHRINK) * (1.0 / WENO_SHRINK);
+    }
+    return weno5_pair<M>(P, N, WENO_C1);
+}
+
+// Magnitudes compared by their high words, read as FP32 numbers: ordered as the values are (up
+// to 2^1017). raise(): the largest of m, |x| and |y| (one instruction; fmaxf() would first
+// quiet its operands).
+__device__ __forceinline__ float high_float(double x) {
+    return __uint_as_float((unsigned)(__double_as_longlong(x) >> 32));
+}
+__device__ __forceinline__ void raise(float& m, double x, double y) {
+    asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(m) : "v"(high_float(x)), "v"(high_float(y)));
+}
+// Whether fluxes of values up to mu (the pressure among them) at speeds up to mv (one at
+// least), so raised, need WENO_SHRINK. Split fluxes are within 1.5 mu mv; the sum of the high
+// words is the logarithm of the product to 0.18, and 2^58.18 * 1.5 < 2^59.
+__device__ __forceinline__ bool flux_wide(float mu, float mv) {
+    return __float_as_uint(mu) + __float_as_uint(mv) >= (2u * 1023u + 58u) << 20;
 }
 
 __device__ __forceinline__ double rk_combine(int stage, double u0, double us, double L, double dt) {

@@ -99,11 +99,11 @@ constexpr int stage_left(int nu) { return nu % STAGE_W <= 2 ? nu % STAGE_W : 0; 
 constexpr int SMALL_SPLIT = 4;
 
 // LDS doubles of a stage workgroup: u, v, p (detailed model: times SPLIT_SCALE), source and
-// flags (32 bits each) of every point, one split-flux buffer per wave.
+// flags (32 bits each) of every point, one split-flux buffer and one word (wide) per wave.
 template <int TX, int TY>
 constexpr int stage_lds(int waves) {
     return 3 * Geom<TX, TY>::NPP + Geom<TX, TY>::NPP + waves * Geom<TX, TY>::BUF +
-           (Geom<TX, TY>::R == 1 ? 64 : 0);
+           (Geom<TX, TY>::R == 1 ? 64 : 0) + (waves + 1) / 2;
 }
 
 // Point p of a tile of tw x th valid cells: its tile-local position and whether the x
@@ -176,6 +176,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs& a, const int ti, con
     double* bufs = pp + NPP;
     unsigned* psrc = (unsigned*)(bufs + W * G::BUF);
     unsigned* pfl = psrc + NPP;   // flags, and in the high half the place of a halo point in its strip
+    unsigned* pwide = (unsigned*)(bufs + W * G::BUF + NPP + (R == 1 ? 64 : 0));   // one word per wave
     double* psr = bufs + W * G::BUF + NPP;   // (R == 1) explicit source of the cells
 
     // ---------------- phase 0: source and primitives of every point of the tile and its halo
@@ -246,12 +247,13 @@ __device__ __forceinline__ void stage_tile(const StageArgs& a, const int ti, con
                                       : (stage == 1) ? step_dt(a, B.domain, 0) : a.dt[B.domain]);
     if (!(dt > 0.0)) return;   // finished domain: state unchanged
     // 1 / (dx0 / 2^lev): scaling by a power of two is exact
-    const double idx = uniform(ldexp(D.idx0, lev)), idy = uniform(ldexp(D.idy0, lev));
+    double idx = uniform(ldexp(D.idx0, lev)), idy = uniform(ldexp(D.idy0, lev));
     const double ax = uniform(slot_get(a.red, bin, 2 * slot));
     const double ay = uniform(slot_get(a.red, bin, 2 * slot + 1));
-    const double sax = uniform(scale * ax), say = uniform(scale * ay);
+    double sax = uniform(scale * ax), say = uniform(scale * ay);
     const double Town = Tr[0];   // T of the cell this thread solves in phase 2
     double src_e = 0.0;          // its explicit source, one-step model (Sec. 4.3)
+    float mu = 0.0f, mv = high_float(1.0);   // largest values and speeds (flux_wide)
     double uleft[LEFT + 1];      // its left-over components
 #pragma unroll
     for (int k = 0; k < LEFT; ++k) uleft[k] = ur[0][NR + k];
@@ -279,6 +281,12 @@ __device__ __forceinline__ void stage_tile(const StageArgs& a, const int ti, con
                 split_flux<M>(uk, scale * vy, say, 0.0, Y[o], Y[G::NY + o], uk);
             }
         }
+        if constexpr (DET) {
+#pragma unroll
+            for (int f = 0; f < NU; f += 2) raise(mu, ur[k][f], f + 1 < NU ? ur[k][f + 1] : pr);
+            if (NU % 2 == 0) raise(mu, pr, pr);
+            raise(mv, vx, vy);
+        }
         if constexpr (M == ONESTEP) {
             if (k == 0) {
                 const double Tc = pr / (ur[k][0] * D.R);
@@ -297,6 +305,11 @@ __device__ __forceinline__ void stage_tile(const StageArgs& a, const int ti, con
             place = (unsigned)(p < G::NC + G::NHX ? lj * G::PX + li + 3 : (lj + 3) * G::PY + li);
         }
         pfl[p] = pfl0[k] | place << 16;
+    }
+    if constexpr (DET) {
+        raise(mv, ax, ay);
+        const bool any = __any(flux_wide(mu, mv));
+        if ((tid & 63) == 0) pwide[tid >> 6] = any ? 1u : 0u;
     }
     __syncthreads();
 
@@ -327,24 +340,29 @@ __device__ __forceinline__ void stage_tile(const StageArgs& a, const int ti, con
     // RK stage (Shu-Osher): ca U^n + cb (U + dt L)
     const double ca = (stage == 1) ? 0.0 : (stage == 2) ? 0.75 : 1.0 / 3.0;
     const double cb = (stage == 1) ? 1.0 : (stage == 2) ? 0.25 : 2.0 / 3.0;
+    // The tile's fluxes are reconstructed at WENO_SHRINK times their value.
+    // (Cost against no test at all: 9 species, 0 to 1 % of the steps; 2 species, 700 k cells, 3 %.
+    // A test of every denominator took 1.4 % of the former and 7 % where launches are short.)
+    bool wide = false;
+    if constexpr (DET) {
+        unsigned h = 0u;
+#pragma unroll
+        for (int q = 0; q < W; ++q) h |= pwide[q];
+        wide = __builtin_amdgcn_readfirstlane(h) != 0u;
+    }
     if constexpr (LEFT > 0) {   // components left over: wave w takes interface w of every run
         double hx[LEFT], hy[LEFT], he[LEFT];
 #pragma unroll
         for (int k = 0; k < LEFT; ++k) {
             const double* X = bufs + 2 * k * G::BUF;
             const double* Y = X + G::BUF;
-            double h1[1];
-            weno5_runs<M, 1, 1>(X + xbase + w, X + G::NX + xbase + w, h1);
-            hx[k] = h1[0];
+            hx[k] = weno5_one<M, 1>(X + xbase + w, X + G::NX + xbase + w, wide);
             hy[k] = he[k] = 0.0;
-            if constexpr (G::TWO) {
-                weno5_runs<M, 1, G::PY>(Y + ybase + w * G::PY, Y + G::NY + ybase + (w + 1) * G::PY, h1);
-                hy[k] = h1[0];
-            }
+            if constexpr (G::TWO)
+                hy[k] = weno5_one<M, G::PY>(Y + ybase + w * G::PY, Y + G::NY + ybase + (w + 1) * G::PY, wide);
             if (tid < G::NEXT) {   // right column, top row
-                if (tid < TY) weno5_runs<M, 1, 1>(X + tid * G::PX + TX, X + G::NX + tid * G::PX + TX, h1);
-                else weno5_runs<M, 1, G::PY>(Y + TY * G::PY + tid - TY, Y + G::NY + (TY + 1) * G::PY + tid - TY, h1);
-                he[k] = h1[0];
+                if (tid < TY) he[k] = weno5_one<M, 1>(X + tid * G::PX + TX, X + G::NX + tid * G::PX + TX, wide);
+                else he[k] = weno5_one<M, G::PY>(Y + TY * G::PY + tid - TY, Y + G::NY + (TY + 1) * G::PY + tid - TY, wide);
             }
             // one component after the other: both at once took 191 registers, two waves per SIMD
             // where one takes three (3 species, 700 k cells: 261 -> 221 us per step)
@@ -375,6 +393,24 @@ __device__ __forceinline__ void stage_tile(const StageArgs& a, const int ti, con
                 a.Uout[(size_t)(NR + k) * a.pool + c] = ca * u0 + cb * (uleft[k] + dt * L);
             }
         }
+        __syncthreads();
+    }
+    double c1 = WENO_C1, escale = 1.0 / scale;
+    if (DET && __builtin_expect(wide, 0)) {
+#pragma unroll
+        for (int k = 0; k < NT; ++k) {
+            const int p = tid + 64 * W * k;
+            if (p >= NPP) continue;
+            pu[p] *= WENO_SHRINK;
+            pv[p] *= WENO_SHRINK;
+            pp[p] *= WENO_SHRINK;
+        }
+        sax = uniform(sax * WENO_SHRINK);
+        say = uniform(say * WENO_SHRINK);
+        c1 = WENO_C1 * WENO_SHRINK * WENO_SHRINK;
+        escale = 1.0 / (scale * WENO_SHRINK);
+        idx = uniform(idx * (1.0 / WENO_SHRINK));
+        idy = uniform(idy * (1.0 / WENO_SHRINK));
         __syncthreads();
     }
     // component f of the lane's points
@@ -424,7 +460,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs& a, const int ti, con
             if (!plain) {
                 const double p = pp[64 * q + l];
                 if constexpr (DET) {
-                    F = (f == 3) ? (p * vn) * (1.0 / scale) : p;
+                    F = (f == 3) ? (p * vn) * escale : p;
                 } else {
                     ue += (f == 3) ? p : 0.0;
                     F = (f == 3) ? 0.0 : p;
@@ -477,7 +513,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs& a, const int ti, con
                     eM[k] = S[G::NX + o + 4 - k];
                 }
             }
-            weno5_runs<M, R, 1>(S + xbase, S + G::NX + xbase, hx);
+            weno5_runs<M, R, 1>(S + xbase, S + G::NX + xbase, hx, c1);
         }
         wave_sync();
         // y pass
@@ -504,18 +540,18 @@ __device__ __forceinline__ void stage_tile(const StageArgs& a, const int ti, con
                     tM[k] = SY[TY * G::PY + l + (5 - k) * G::PY];
                 }
             }
-            weno5_runs<M, R, G::PY>(S + ybase, SY + G::PY + ybase, h);
+            weno5_runs<M, R, G::PY>(S + ybase, SY + G::PY + ybase, h, c1);
 #pragma unroll
             for (int k = 0; k < R; ++k) hy[k] = h[k];
             wave_sync();
             SH[(l / TX) * TX + oli] = h[0];
-            if constexpr (G::NEXT > 64) SH[(TY / R) * TX + l] = weno5_pair<M>(tP, tM);
+            if constexpr (G::NEXT > 64) SH[(TY / R) * TX + l] = weno5_pair<M>(tP, tM, c1);
         }
         // numerical fluxes to LDS, the right column and top row with them
 #pragma unroll
         for (int k = 0; k < R; ++k) S[(l / G::XR) * G::HX + (l % G::XR) * R + k] = hx[k];
         if (G::NEXT > 64 ? l < TY : l < G::NEXT) {
-            const double he = weno5_pair<M>(eP, eM);
+            const double he = weno5_pair<M>(eP, eM, c1);
             if (l < TY) S[l * G::HX + TX] = he;
             else SH[(TY / R) * TX + l - TY] = he;
         }
@@ -540,6 +576,10 @@ __device__ __forceinline__ void stage_tile(const StageArgs& a, const int ti, con
             if ((own >> q) & 1u) out[sp[q]] = unew;
         }
         wave_sync();
+    }
+    if (DET && __builtin_expect(wide, 0)) {
+        idx = uniform(idx * WENO_SHRINK);
+        idy = uniform(idy * WENO_SHRINK);
     }
     __syncthreads();   // the new state of the tile is complete (in the caches)
 
@@ -581,11 +621,12 @@ __device__ __forceinline__ void stage_tile(const StageArgs& a, const int ti, con
     }
 }
 
-#ifndef STAGE_WAVES
-#define STAGE_WAVES 1
-#endif
+// Waves per SIMD that the registers have to leave room for: with 2 and 3 species the 16 x 16
+// kernel takes about 128 registers, and one more costs the fourth wave.
+template <int M, int NU, int TX>
+constexpr int stage_waves() { return (M == DETAILED && NU <= 6 && TX == 16) ? 4 : 1; }
 template <int M, int NU, int TX, int TY, bool HAS1D, bool HAS2D>
-__global__ __launch_bounds__(64 * STAGE_W, STAGE_WAVES) void stage_kernel(StageArgs a, int first_tile, int owner_launch) {
+__global__ __launch_bounds__(64 * STAGE_W, (stage_waves<M, NU, TX>())) void stage_kernel(StageArgs a, int first_tile, int owner_launch) {
     constexpr int L2 = HAS2D ? stage_lds<TX, TY>(STAGE_W) : 0, L1 = HAS1D ? stage_lds<256, 1>(STAGE_W) : 0;
     __shared__ __align__(16) double smem[(L2 > L1) ? L2 : L1];
     if (blockIdx.x == 0) stage_bookkeeping(a, owner_launch);
