@@ -31,6 +31,7 @@ struct janc_plan;
 
 struct janc_ctx {
     int device = 0;
+    int cus = 0;                  // compute units of the device
     int model = 0;
     int ns = 0;
     int nU = 0;
@@ -961,18 +962,33 @@ janc_status autotune(janc_ctx* c, janc_plan* P, const janc_time* tm, double* U, 
 // Whole runs of tiny domains in one launch: every domain 1-D, one block on one level, at most
 // run_cells() cells, a model without chemistry solves, and no flag that asks for a form of
 // its own. Larger domains take one launch per stage.
+//
+// A run lasts as long as the largest domain needs, times the turns that the domains take, where
+// a stage launch lasts as long as all tiles together: with more domains than fit at once, the
+// domains have to be of like size. us per step of the run / of launches per stage, gas without
+// chemistry: 8192 x 50 cells 54 / 204, 2048 x 300 80 / 115, 2048 x 700 139 / 164; 255 x 40 and
+// 1 x 700 (one turn) 17 / 26; 512 x 40 and 512 x 300 (two turns) 47 / 53, 2048 of each (six
+// turns) 159 / 159; 300 x 40 and 1 x 700 25 / 27, 1024 x 40 and 1 x 700 48 / 41; one-step,
+// 2048 x 300 and 2048 x 700 343 / 335.
 bool tiny_domains(const janc_ctx* c, const janc_plan* P) {
     if (c->model == DETAILED || (P->flags & ~JANC_PLAN_NO_GRAPH) || P->nblk != P->ndom) return false;
+    int cells = 0;
+    long long sum = 0;
     for (int d = 0; d < P->ndom; ++d) {
         const DevBlock& b = P->hblk[d];
         if (b.domain != d || P->hdom[d].nlevels != 1 || P->hdom[d].twod || b.nx > run_cells(c->model))
             return false;
+        cells = std::max(cells, b.nx);
+        sum += b.nx;
     }
-    return true;
+    const int rounds = run_shape(c->model, cells, P->ndom, c->cus).rounds;
+    const double fill = (double)sum / ((double)P->ndom * cells);
+    return rounds == 1 || fill >= (rounds == 2 ? 0.5 : 0.75);
 }
 
-// Steps of one launch: the state goes through memory between launches, so the count does
-// not show in the results; it bounds the length of a launch (about 20 ms).
+// Steps of one launch, times the turns of the chip that its domains take: the state goes
+// through memory between launches, so the count does not show in the results; it bounds the
+// length of a launch (2,048 steps of the longest domains, 24 us each: 50 ms).
 constexpr int RUN_STEPS = 2048;
 
 janc_status run_tiny(janc_ctx* c, janc_plan* P, const janc_time* tm, double* U, double* T, int nsteps,
@@ -1003,10 +1019,12 @@ janc_status run_tiny(janc_ctx* c, janc_plan* P, const janc_time* tm, double* U, 
     }
     int cells = 0;
     for (int d = 0; d < P->ndom; ++d) cells = std::max(cells, P->hblk[d].nx);
-    for (int n0 = 0; n0 < nsteps; n0 += RUN_STEPS) {
+    const RunShape shape = run_shape(c->model, cells, P->ndom, c->cus);
+    const int steps = std::max(1, RUN_STEPS / shape.rounds);
+    for (int n0 = 0; n0 < nsteps; n0 += steps) {
         a.step0 = n0;
-        a.nsteps = std::min(RUN_STEPS, nsteps - n0);
-        HIPCHK(c, launch_run(c->model, a, cells, s), "run launch");
+        a.nsteps = std::min(steps, nsteps - n0);
+        HIPCHK(c, launch_run(c->model, a, shape, s), "run launch");
     }
     return JANC_OK;
 }
@@ -1690,6 +1708,8 @@ janc_status janc_create(janc_ctx** out, int model, const janc_mech* mech, int de
     if (hipGetDeviceCount(&ndev) != hipSuccess || device < 0 || device >= ndev) return JANC_EHIP;
     if (hipSetDevice(device) != hipSuccess) return JANC_EHIP;
     c->device = device;
+    if (hipDeviceGetAttribute(&c->cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || c->cus < 1)
+        return JANC_EHIP;
     c->model = model;
     if (model == DETAILED) {
         janc_status st = build_mech(c.get(), mech);

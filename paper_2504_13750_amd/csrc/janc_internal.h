@@ -171,10 +171,15 @@ hipError_t launch_clear_reduce(const Reduce& r, int which, hipStream_t s);
 hipError_t launch_zero_int(int* p, hipStream_t s);
 hipError_t launch_stage(int model, int ns, int kind_mask, int tile_w, const StageArgs& a,
                         int first_tile, int ntiles, hipStream_t s);
-// (1-D domains of the models CPG and ONESTEP; cells: of the largest domain, at most
-// run_cells(model))
+// (1-D domains of the models CPG and ONESTEP; cells: of the largest domain, 1 .. run_cells(model))
 int run_cells(int model);
-hipError_t launch_run(int model, const RunArgs& a, int cells, hipStream_t s);
+struct RunShape {
+    int cap;                  // cells that the kernel's LDS holds
+    int threads;              // of a workgroup
+    int rounds;               // turns of the chip that the domains take
+};
+RunShape run_shape(int model, int cells, int ndom, int cus);
+hipError_t launch_run(int model, const RunArgs& a, const RunShape& r, hipStream_t s);
 hipError_t launch_init(int model, int ns, int tile_w, const StageArgs& a, hipStream_t s);
 // Tile width of launch_stage and the halo table that asks for quarter tiles.
 constexpr int QUARTER_TILES = 8;

@@ -1241,9 +1241,13 @@ __global__ void prim_to_cons_kernel(const DevMech* mech, double gamma, double R,
 // us per stage; 10.7 us with 256-cell tiles).
 constexpr int RUN_CELLS = 1023;   // one thread per interface
 
-template <int M, int NU>
+// LDS bytes of a run over up to `cap` cells: RUN_CELLS takes 99 and 124 KB, one workgroup per
+// CU. Kernels of half, a quarter and an eighth of that let shorter domains share a CU.
+constexpr int run_lds(int nu, int cap) { return 8 * (nu * (2 * (cap + 6) + cap + 1) + 96 + 2 * (nu + 3)); }
+
+template <int M, int NU, int CAP>
 __global__ __launch_bounds__(1024) void run_kernel(RunArgs A) {
-    constexpr int NS = RUN_CELLS + 6, NH = RUN_CELLS + 1;
+    constexpr int NS = CAP + 6, NH = CAP + 1;
     __shared__ double fp[NU * NS], fm[NU * NS], hf[NU * NH];
     __shared__ double smax[2][3][16];             // |u|+c, |v|+c, CFL bound of each wave
     __shared__ double dirs[2][NU + 3];            // Dirichlet sides: state, u, v, p

@@ -1,6 +1,8 @@
 // janc_kernels.hip -- launchers of the JANC step kernels (janc_kernels.h): the
 // calorically perfect and one-step models here, the detailed model through the
 // per-species-count launch tables of janc_species.hip.
+#include <algorithm>
+
 #include "janc_launch.h"
 
 namespace janc {
@@ -107,13 +109,38 @@ hipError_t launch_halo_table(int tile_w, const StageArgs& a, int* out, int strid
 // (Two-dimensional domains were slower from 16 x 16 cells on, 25.3 / 29.8.)
 int run_cells(int model) { return model == CPG ? RUN_CELLS : model == ONESTEP ? 704 : 0; }
 
-hipError_t launch_run(int model, const RunArgs& a, int cells, hipStream_t s) {
-    if (cells < 1 || cells > run_cells(model)) return hipErrorInvalidValue;
-    // whole groups of waves for the interfaces of up to all components
+// Threads of a workgroup: whole groups of waves for the interfaces of up to all components, and
+// no more groups than the chip's wave slots (16 per CU at these registers) have room for: with
+// fewer slots than groups, the components of one domain in turn and more domains at once.
+RunShape run_shape(int model, int cells, int ndom, int cus) {
     const int nu = model == CPG ? 4 : 5, m = (cells + 64) / 64 * 64;
-    const int threads = max((cells + 63) / 64 * 64, m * min(nu, 1024 / m));
-    if (model == CPG) run_kernel<CPG, 4><<<a.ndom, threads, 0, s>>>(a);
-    else run_kernel<ONESTEP, 5><<<a.ndom, threads, 0, s>>>(a);
+    RunShape r;
+    r.cap = cells <= 127 ? 127 : cells <= 255 ? 255 : cells <= 511 && ndom > cus ? 511 : RUN_CELLS;
+    const int fit = 160 * 1024 / run_lds(nu, r.cap);   // workgroups of a CU by their LDS
+    int groups = std::min(nu, 1024 / m);
+    while (groups > 1 && std::min(fit, 1024 / (m * groups)) < fit &&
+           (long long)ndom > (long long)cus * std::min(fit, 1024 / (m * groups)))
+        --groups;
+    r.threads = std::max((cells + 63) / 64 * 64, m * groups);
+    const long long at_once = (long long)cus * std::min(fit, 1024 / r.threads);
+    r.rounds = (int)((ndom + at_once - 1) / at_once);
+    return r;
+}
+
+template <int M, int NU>
+void launch_run_m(const RunArgs& a, const RunShape& r, hipStream_t s) {
+    switch (r.cap) {
+        case 127: run_kernel<M, NU, 127><<<a.ndom, r.threads, 0, s>>>(a); break;
+        case 255: run_kernel<M, NU, 255><<<a.ndom, r.threads, 0, s>>>(a); break;
+        case 511: run_kernel<M, NU, 511><<<a.ndom, r.threads, 0, s>>>(a); break;
+        default: run_kernel<M, NU, RUN_CELLS><<<a.ndom, r.threads, 0, s>>>(a);
+    }
+}
+
+hipError_t launch_run(int model, const RunArgs& a, const RunShape& r, hipStream_t s) {
+    if (run_cells(model) == 0) return hipErrorInvalidValue;
+    if (model == CPG) launch_run_m<CPG, 4>(a, r, s);
+    else launch_run_m<ONESTEP, 5>(a, r, s);
     return hipGetLastError();
 }
 
