@@ -103,10 +103,14 @@ hipError_t launch_halo_table(int tile_w, const StageArgs& a, int* out, int strid
     return hipGetLastError();
 }
 
-// Largest 1-D domain that runs in one workgroup. Measured, us per step of one launch per
-// stage / one run: gas without chemistry 50 cells 22.6 / 8.3, 400 cells 23.9 / 13.4, 1024 cells
-// 24.0 / 20.5; one-step 256 cells 25.4 / 15.5, 700 cells 25.8 / 23.8, 1000 cells 25.8 / 28.4.
-// (Two-dimensional domains were slower from 16 x 16 cells on, 25.3 / 29.8.)
+// Largest 1-D domain that runs in one workgroup. Measured, us per step of launches per stage /
+// of the run. 64 domains: gas without chemistry 50 cells 21.4 / 7.7, 400 cells 21.6 / 13.1, 1023
+// cells 22.3 / 20.2; one-step 256 cells 19.8 / 12.8, 511 cells 25.4 / 16.0, 704 cells 25.3 / 21.2.
+// One domain alone, in long calls: 400 cells 19.2 / 12.8, 700 cells 18.8 / 16.9, 1023 cells
+// 17.9 / 19.7; one-step 511 cells 20.5 / 15.7, 700 cells 19.3 / 20.7. There the largest sizes
+// are 4 to 12 % faster in launches per stage, but a call of one step is not (1023 cells 44 / 37,
+// allocation-free 67 / 34; one-step 700 cells 48 / 38; even at 8 to 16 steps).
+// (Two-dimensional domains were slower from 16 x 16 cells on.)
 int run_cells(int model) { return model == CPG ? RUN_CELLS : model == ONESTEP ? 704 : 0; }
 
 // Threads of a workgroup: whole groups of waves for the interfaces of up to all components, and

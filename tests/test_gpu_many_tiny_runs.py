@@ -22,6 +22,11 @@ pytestmark = pytest.mark.gpu
     (MODEL_ONESTEP, [256], (BC_PERIODIC, BC_PERIODIC), 10),
     (MODEL_ONESTEP, [511, 64], (BC_SLIPWALL, BC_ZEROGRAD), 10),
     (MODEL_CPG, [512], (BC_ZEROGRAD, BC_DIRICHLET), 10),
+    (MODEL_ONESTEP, [512], (BC_ZEROGRAD, BC_DIRICHLET), 10),      # the largest alone and one more
+    (MODEL_CPG, [767], (BC_SLIPWALL, BC_DIRICHLET), 10),
+    (MODEL_CPG, [768], (BC_SLIPWALL, BC_DIRICHLET), 10),
+    (MODEL_CPG, [1023] * 20, (BC_PERIODIC, BC_PERIODIC), 4),      # the largest of many
+    (MODEL_ONESTEP, [704] * 30, (BC_SLIPWALL, BC_DIRICHLET), 4),
     (MODEL_CPG, [63] * 700, (BC_ZEROGRAD, BC_DIRICHLET), 6),      # two groups of waves
     (MODEL_ONESTEP, [64] * 1100, (BC_SLIPWALL, BC_SLIPWALL), 6),
     (MODEL_ONESTEP, [20, 9, 17] * 1700, (BC_PERIODIC, BC_PERIODIC), 1030),   # two turns, two launches
