@@ -65,6 +65,12 @@ struct janc_ctx {
     std::string adj_chem_log;
 };
 
+// A launch of whole runs of tiny domains: `count` domains from drun[first].
+struct RunClass {
+    int first, count;
+    RunShape shape;
+};
+
 struct janc_plan {
     janc_ctx* ctx = nullptr;
     int flags = 0;
@@ -93,6 +99,8 @@ struct janc_plan {
     int* dmap = nullptr;
     Tile* dtiles = nullptr;
     int* dhsrc = nullptr;          // halo source table (StageArgs::hsrc), or null
+    std::vector<RunClass> runs;    // tiny domains: the launches of a whole run; else empty
+    int* drun = nullptr;           // their domains, or null: one launch over all in order
     int* arena_hsrc = nullptr;     // arena: where a call with several steps builds the table
     int hstride = 0;
     double* ddir = nullptr;
@@ -174,7 +182,7 @@ void plan_free(janc_plan* p) {
     if (!p) return;
     if (!p->arena) {
         void* ptrs[] = {p->ddom, p->dblk, p->dmap, p->dtiles, p->dhsrc, p->ddir, p->dred, p->ddt,
-                        p->dstep, p->dfine, p->dring, p->U1, p->U2, p->T1, p->T2};
+                        p->dstep, p->dfine, p->dring, p->drun, p->U1, p->U2, p->T1, p->T2};
         for (void* q : ptrs)
             if (q) hipFree(q);
     }
@@ -277,6 +285,41 @@ janc_status upload_mech(janc_ctx* c) {
 struct LevelMap {
     int w8 = 0, h8 = 0, off = 0;
 };
+
+// Whole runs of tiny domains: every domain 1-D, one block on one level, at most run_cells()
+// cells, a model without chemistry solves, and no flag that asks for a form of its own. Larger
+// domains take one launch per stage.
+//
+// A launch lasts as long as its largest domain needs, times the turns that its domains take.
+// Where all domains fit at once they take one launch, else one for each LDS capacity, the
+// larger domains first. us per step of the run / of launches per stage, gas without chemistry:
+// 8192 x 50 cells 54 / 204, 2048 x 300 80 / 115, 2048 x 700 139 / 164, 255 x 40 and 1 x 700 17 /
+// 26 (one launch), 1024 x 40 and 1 x 700 28 / 42 (two; 47 in one), one-step 2048 x 300 and
+// 2048 x 700 261 / 331 (340 in one).
+janc_status plan_runs(janc_ctx* c, janc_plan* P) {
+    if (c->model == DETAILED || (P->flags & ~JANC_PLAN_NO_GRAPH) || P->nblk != P->ndom) return JANC_OK;
+    int cells = 0;
+    std::vector<int> order(P->ndom);
+    for (int d = 0; d < P->ndom; ++d) {
+        const DevBlock& b = P->hblk[d];
+        if (b.domain != d || P->hdom[d].nlevels != 1 || P->hdom[d].twod || b.nx > run_cells(c->model))
+            return JANC_OK;
+        cells = std::max(cells, b.nx);
+        order[d] = d;
+    }
+    const RunShape all = run_shape(c->model, cells, P->ndom, c->cus);
+    if (all.rounds == 1) {
+        P->runs.push_back(RunClass{0, P->ndom, all});
+        return JANC_OK;
+    }
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return P->hblk[a].nx > P->hblk[b].nx; });
+    auto cap = [&](int q) { return run_cap(P->hblk[order[q]].nx, true); };
+    for (int q = 0, e; q < P->ndom; q = e) {
+        for (e = q; e < P->ndom && cap(e) == cap(q);) ++e;
+        P->runs.push_back(RunClass{q, e - q, run_shape(c->model, P->hblk[order[q]].nx, e - q, c->cus)});
+    }
+    return pupload(P, &P->drun, order);
+}
 
 janc_status build_plan(janc_ctx* c, int nd, const janc_domain* doms, int nb, const janc_block* blocks,
                        long long pool, int flags, janc_plan** out, char* arena = nullptr,
@@ -515,6 +558,7 @@ janc_status build_plan(janc_ctx* c, int nd, const janc_domain* doms, int nb, con
     }
     if ((st = pupload(P.get(), &P->dfine, P->fine_flat))) return st;
     if ((st = pupload(P.get(), &P->dring, P->ring_blocks))) return st;
+    if ((st = plan_runs(c, P.get()))) return st;
     P->red_stride = 2 * P->nunits + nd;
     const int ntrip = (flags & JANC_PLAN_CROSSOVER) ? P->maxlev + 1 : 1;   // slot sets
     if ((st = palloc(P.get(), &P->dred, (size_t)RED_BUFS * ntrip * P->red_stride * SLOT_WORDS))) return st;
@@ -959,33 +1003,6 @@ janc_status autotune(janc_ctx* c, janc_plan* P, const janc_time* tm, double* U, 
     return JANC_OK;
 }
 
-// Whole runs of tiny domains in one launch: every domain 1-D, one block on one level, at most
-// run_cells() cells, a model without chemistry solves, and no flag that asks for a form of
-// its own. Larger domains take one launch per stage.
-//
-// A run lasts as long as the largest domain needs, times the turns that the domains take, where
-// a stage launch lasts as long as all tiles together: with more domains than fit at once, the
-// domains have to be of like size. us per step of the run / of launches per stage, gas without
-// chemistry: 8192 x 50 cells 54 / 204, 2048 x 300 80 / 115, 2048 x 700 139 / 164; 255 x 40 and
-// 1 x 700 (one turn) 17 / 26; 512 x 40 and 512 x 300 (two turns) 47 / 53, 2048 of each (six
-// turns) 159 / 159; 300 x 40 and 1 x 700 25 / 27, 1024 x 40 and 1 x 700 48 / 41; one-step,
-// 2048 x 300 and 2048 x 700 343 / 335.
-bool tiny_domains(const janc_ctx* c, const janc_plan* P) {
-    if (c->model == DETAILED || (P->flags & ~JANC_PLAN_NO_GRAPH) || P->nblk != P->ndom) return false;
-    int cells = 0;
-    long long sum = 0;
-    for (int d = 0; d < P->ndom; ++d) {
-        const DevBlock& b = P->hblk[d];
-        if (b.domain != d || P->hdom[d].nlevels != 1 || P->hdom[d].twod || b.nx > run_cells(c->model))
-            return false;
-        cells = std::max(cells, b.nx);
-        sum += b.nx;
-    }
-    const int rounds = run_shape(c->model, cells, P->ndom, c->cus).rounds;
-    const double fill = (double)sum / ((double)P->ndom * cells);
-    return rounds == 1 || fill >= (rounds == 2 ? 0.5 : 0.75);
-}
-
 // Steps of one launch, times the turns of the chip that its domains take: the state goes
 // through memory between launches, so the count does not show in the results; it bounds the
 // length of a launch (2,048 steps of the longest domains, 24 us each: 50 ms).
@@ -1017,14 +1034,14 @@ janc_status run_tiny(janc_ctx* c, janc_plan* P, const janc_time* tm, double* U, 
     } else {
         a.dirU = P->ddir;
     }
-    int cells = 0;
-    for (int d = 0; d < P->ndom; ++d) cells = std::max(cells, P->hblk[d].nx);
-    const RunShape shape = run_shape(c->model, cells, P->ndom, c->cus);
-    const int steps = std::max(1, RUN_STEPS / shape.rounds);
-    for (int n0 = 0; n0 < nsteps; n0 += steps) {
-        a.step0 = n0;
-        a.nsteps = std::min(steps, nsteps - n0);
-        HIPCHK(c, launch_run(c->model, a, shape, s), "run launch");
+    for (const RunClass& r : P->runs) {
+        a.order = P->drun ? P->drun + r.first : nullptr;
+        const int steps = std::max(1, RUN_STEPS / r.shape.rounds);
+        for (int n0 = 0; n0 < nsteps; n0 += steps) {
+            a.step0 = n0;
+            a.nsteps = std::min(steps, nsteps - n0);
+            HIPCHK(c, launch_run(c->model, a, r.count, r.shape, s), "run launch");
+        }
     }
     return JANC_OK;
 }
@@ -1043,7 +1060,7 @@ janc_status run_steps(janc_ctx* c, janc_plan* P, const janc_time* tm, double* U,
         janc_status st = autotune(c, P, tm, U, T, 5, nullptr, s);
         if (st) return st;
     }
-    if (nsteps > 0 && tiny_domains(c, P)) return run_tiny(c, P, tm, U, T, nsteps, t, dt_log, s);
+    if (nsteps > 0 && !P->runs.empty()) return run_tiny(c, P, tm, U, T, nsteps, t, dt_log, s);
     const StageArgs base = base_args(P, tm, U, T, t, dt_log, nsteps);
     HIPCHK(c, launch_zero_int(P->dstep, s), "counter launch");
     StageArgs a0 = base;
@@ -1182,7 +1199,7 @@ janc_status run_step_noalloc(janc_ctx* c, const janc_grid* g, const janc_physics
     }
     janc_plan* P = c->nplan;
     P->dhsrc = nullptr;
-    if (!(nsteps > 0 && tiny_domains(c, P))) {
+    if (!(nsteps > 0 && !P->runs.empty())) {
         st = stage_tables(c, P, s);
         if (st) return st;
         // A step whose stages look their halo sources up takes 3.4 us longer (one-step 64 x 16

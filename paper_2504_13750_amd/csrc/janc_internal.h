@@ -146,6 +146,7 @@ struct StageArgs {
 struct RunArgs {
     const DevDomain* dom;     // [ndom], or null: the one domain dom0
     const DevBlock* blk;      // [ndom], block d covers domain d; or null: offset 0
+    const int* order;         // domain of each workgroup, or null: the workgroup's number
     const double* dirU;       // Dirichlet rows, or null: prim
     double *U, *T, *t;
     long long pool;
@@ -179,7 +180,8 @@ struct RunShape {
     int rounds;               // turns of the chip that the domains take
 };
 RunShape run_shape(int model, int cells, int ndom, int cus);
-hipError_t launch_run(int model, const RunArgs& a, const RunShape& r, hipStream_t s);
+int run_cap(int cells, bool many);
+hipError_t launch_run(int model, const RunArgs& a, int count, const RunShape& r, hipStream_t s);
 hipError_t launch_init(int model, int ns, int tile_w, const StageArgs& a, hipStream_t s);
 // Tile width of launch_stage and the halo table that asks for quarter tiles.
 constexpr int QUARTER_TILES = 8;

@@ -1251,7 +1251,7 @@ __global__ __launch_bounds__(1024) void run_kernel(RunArgs A) {
     __shared__ double fp[NU * NS], fm[NU * NS], hf[NU * NH];
     __shared__ double smax[2][3][16];             // |u|+c, |v|+c, CFL bound of each wave
     __shared__ double dirs[2][NU + 3];            // Dirichlet sides: state, u, v, p
-    const int d = blockIdx.x, tid = threadIdx.x, l = tid & 63;
+    const int d = A.order ? A.order[blockIdx.x] : (int)blockIdx.x, tid = threadIdx.x, l = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     // the scalars of the domain
     DevDomain D{};

@@ -113,13 +113,17 @@ hipError_t launch_halo_table(int tile_w, const StageArgs& a, int* out, int strid
 // (Two-dimensional domains were slower from 16 x 16 cells on.)
 int run_cells(int model) { return model == CPG ? RUN_CELLS : model == ONESTEP ? 704 : 0; }
 
+// LDS capacity (cells) of the kernel for the largest domain. (511 only with more domains than
+// CUs: alone, a 400-cell tube took 1279 us in place of 1268.)
+int run_cap(int cells, bool many) { return cells <= 127 ? 127 : cells <= 255 ? 255 : cells <= 511 && many ? 511 : RUN_CELLS; }
+
 // Threads of a workgroup: whole groups of waves for the interfaces of up to all components, and
 // no more groups than the chip's wave slots (16 per CU at these registers) have room for: with
 // fewer slots than groups, the components of one domain in turn and more domains at once.
 RunShape run_shape(int model, int cells, int ndom, int cus) {
     const int nu = model == CPG ? 4 : 5, m = (cells + 64) / 64 * 64;
     RunShape r;
-    r.cap = cells <= 127 ? 127 : cells <= 255 ? 255 : cells <= 511 && ndom > cus ? 511 : RUN_CELLS;
+    r.cap = run_cap(cells, ndom > cus);
     const int fit = 160 * 1024 / run_lds(nu, r.cap);   // workgroups of a CU by their LDS
     int groups = std::min(nu, 1024 / m);
     while (groups > 1 && std::min(fit, 1024 / (m * groups)) < fit &&
@@ -132,19 +136,19 @@ RunShape run_shape(int model, int cells, int ndom, int cus) {
 }
 
 template <int M, int NU>
-void launch_run_m(const RunArgs& a, const RunShape& r, hipStream_t s) {
+void launch_run_m(const RunArgs& a, int count, const RunShape& r, hipStream_t s) {
     switch (r.cap) {
-        case 127: run_kernel<M, NU, 127><<<a.ndom, r.threads, 0, s>>>(a); break;
-        case 255: run_kernel<M, NU, 255><<<a.ndom, r.threads, 0, s>>>(a); break;
-        case 511: run_kernel<M, NU, 511><<<a.ndom, r.threads, 0, s>>>(a); break;
-        default: run_kernel<M, NU, RUN_CELLS><<<a.ndom, r.threads, 0, s>>>(a);
+        case 127: run_kernel<M, NU, 127><<<count, r.threads, 0, s>>>(a); break;
+        case 255: run_kernel<M, NU, 255><<<count, r.threads, 0, s>>>(a); break;
+        case 511: run_kernel<M, NU, 511><<<count, r.threads, 0, s>>>(a); break;
+        default: run_kernel<M, NU, RUN_CELLS><<<count, r.threads, 0, s>>>(a);
     }
 }
 
-hipError_t launch_run(int model, const RunArgs& a, const RunShape& r, hipStream_t s) {
+hipError_t launch_run(int model, const RunArgs& a, int count, const RunShape& r, hipStream_t s) {
     if (run_cells(model) == 0) return hipErrorInvalidValue;
-    if (model == CPG) launch_run_m<CPG, 4>(a, r, s);
-    else launch_run_m<ONESTEP, 5>(a, r, s);
+    if (model == CPG) launch_run_m<CPG, 4>(a, count, r, s);
+    else launch_run_m<ONESTEP, 5>(a, count, r, s);
     return hipGetLastError();
 }
 

@@ -1,7 +1,7 @@
 """Whole runs of many tiny one-dimensional domains in one launch: sizes on both sides of every
 LDS capacity, more domains than the chip holds at once (fewer wave groups per domain, several
-turns, fewer steps per launch), and domains of unlike sizes, bitwise equal to the launches per
-stage. The dt log of a call of several launches equals that of calls of one launch each.
+turns, fewer steps per launch), and domains of unlike sizes (a launch for each LDS capacity),
+bitwise equal to the launches per stage. The dt log of a call of several launches equals that of calls of one launch each.
 """
 
 import numpy as np
@@ -32,8 +32,9 @@ pytestmark = pytest.mark.gpu
     (MODEL_ONESTEP, [20, 9, 17] * 1700, (BC_PERIODIC, BC_PERIODIC), 1030),   # two turns, two launches
     (MODEL_CPG, [300, 290] * 400, (BC_SLIPWALL, BC_ZEROGRAD), 6),
     (MODEL_ONESTEP, [600] * 520, (BC_ZEROGRAD, BC_DIRICHLET), 4),
-    (MODEL_CPG, [40] * 600 + [700], (BC_ZEROGRAD, BC_DIRICHLET), 6),   # unlike: launches per stage
-    (MODEL_CPG, [40] * 200 + [700], (BC_ZEROGRAD, BC_DIRICHLET), 6),
+    (MODEL_CPG, [40] * 600 + [700], (BC_ZEROGRAD, BC_DIRICHLET), 6),   # unlike: a launch for each capacity
+    (MODEL_ONESTEP, [40, 700, 200, 300] * 150 + [3], (BC_SLIPWALL, BC_DIRICHLET), 700),
+    (MODEL_CPG, [40] * 200 + [700], (BC_ZEROGRAD, BC_DIRICHLET), 6),   # all at once
 ])
 def test_runs_equal_stage_launches(model, sizes, bc, nsteps):
     case = domains(model, sizes, bc)
