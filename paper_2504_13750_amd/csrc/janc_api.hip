@@ -79,6 +79,7 @@ struct janc_plan {
     int nunits = 0;
     int tile_w = 16;
     bool small = false;           // few tiles: the stages run on quarter tiles (small_tiles)
+    bool tiny = false;            // more, of at most 64 cells each in 8 x 8 or 64 x 1
     int linear_sched = 0;         // 1: workgroup b takes tile b; 0: XCD-contiguous tile runs
     bool tuned = false;           // janc_plan_autotune has chosen tile_w and linear_sched
     int kind_mask = 0;            // bit 0: 2-D tiles present, bit 1: 1-D tiles present
@@ -583,7 +584,9 @@ StageArgs base_args(janc_plan* P, const janc_time* tm, double* U, double* T, dou
 // one-step 4 tiles 38 / 28, 64 tiles 38 / 35, 128 tiles 40 / 45; gas without chemistry 8 tiles
 // (2000 x 1) 26.5 / 23.6, 16 tiles 30 / 26, 64 tiles 31 / 33.
 int small_tiles(int model) { return model == CPG ? 32 : 64; }
-int stage_width(const janc_plan* P) { return P->small ? QUARTER_TILES : P->tile_w; }
+int stage_width(const janc_plan* P) {
+    return P->small ? QUARTER_TILES : P->tiny ? TINY_TILES : P->tile_w;
+}
 
 // Halo source table: for every tile point outside its block or on a coarse-fine ring,
 // the source resolve() gives (level map, block record, coarser level), found once per
@@ -631,6 +634,7 @@ janc_status build_tiles(janc_ctx* c, janc_plan* P) {
     P->lev_count.assign(P->maxlev + 1, 0);
     P->kind_mask = 0;
     const int TX = P->tile_w, TY = 256 / TX;
+    bool fits = true;   // every tile's cells fit into its first quarter
     for (int l = 0; l <= P->maxlev; ++l) {
         P->lev_first[l] = (int)P->htiles.size();
         for (int id = 0; id < P->nblk; ++id) {
@@ -639,10 +643,12 @@ janc_status build_tiles(janc_ctx* c, janc_plan* P) {
             P->tile_first[id] = (int)P->htiles.size();
             if (!P->hdom[h.domain].twod) {
                 for (int x = 0; x < h.nx; x += 256) P->htiles.push_back(Tile{id, x, 0, 1});
+                fits = fits && h.nx <= 64;
                 P->kind_mask |= 2;
             } else {
                 for (int y = 0; y < h.ny; y += TY)
                     for (int x = 0; x < h.nx; x += TX) P->htiles.push_back(Tile{id, x, y, TX << 8});
+                fits = fits && h.nx <= 8 && h.ny <= 8;
                 P->kind_mask |= 1;
             }
             P->tile_count[id] = (int)P->htiles.size() - P->tile_first[id];
@@ -650,6 +656,7 @@ janc_status build_tiles(janc_ctx* c, janc_plan* P) {
         P->lev_count[l] = (int)P->htiles.size() - P->lev_first[l];
     }
     P->small = (int)P->htiles.size() <= small_tiles(c->model) && (TX < 64 || !(P->kind_mask & 1));
+    P->tiny = !P->small && fits;
     if (P->dtiles && !P->arena) hipFree(P->dtiles);
     P->dtiles = nullptr;
     if (janc_status st = pupload(P, &P->dtiles, P->htiles)) return st;

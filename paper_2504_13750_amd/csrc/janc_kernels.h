@@ -164,7 +164,7 @@ template <int M, int NU, int TX, int TY, int W>
 __device__ __forceinline__ void stage_tile(const StageArgs& a, const int ti, const Tile tile, double* smem) {
     using G = Geom<TX, TY>;
     constexpr int R = G::R, NPL = G::NPL, NPP = G::NPP;
-    constexpr int LEFT = (W < NU) ? stage_left(NU) : 0, NR = NU - LEFT;   // components of whole rounds
+    constexpr int LEFT = (R == W && W < NU) ? stage_left(NU) : 0, NR = NU - LEFT;   // components of whole rounds
     static_assert(LEFT == 0 || (R == W && 2 * LEFT <= W),
                   "left-over components: one interface of a run per wave, two buffers each");
     static_assert(64 * W >= G::NC && (R == 1 || R == W), "phase 2: wave w has cell w of every run");
@@ -655,18 +655,23 @@ __device__ __forceinline__ Tile quarter(Tile t, int sub) {
     return t;
 }
 
-// The stage on quarter tiles: workgroup b takes quarter b % 4 of tile b / 4.
-template <int M, int NU, bool HAS1D, bool HAS2D>
-__global__ __launch_bounds__(64 * NU) void stage_small_kernel(StageArgs a, int first_tile, int owner_launch) {
-    constexpr int L2 = HAS2D ? stage_lds<8, 8>(NU) : 0, L1 = HAS1D ? stage_lds<64, 1>(NU) : 0;
+// The stage on tiles of 64 cells, W waves each. SPLIT = SMALL_SPLIT: quarter tiles, one wave per
+// component; workgroup b takes quarter b % 4 of tile b / 4. SPLIT = 1: plans of many tiles whose
+// valid cells all fit into the first quarter (blocks of up to 8 x 8 or 64 x 1 cells), four
+// waves, as many workgroups as a CU holds; the whole tiles sweep 256 cells for at most 64 of
+// them (us per step, whole / these: 9 species 1000 x 50 cells 105 / 75, 4000 x 8 x 8 446 / 287, 3
+// species 4000 x 50 167 / 115, one-step 4000 x 8 x 8 211 / 124).
+template <int M, int NU, int W, int SPLIT, bool HAS1D, bool HAS2D>
+__global__ __launch_bounds__(64 * W) void stage_small_kernel(StageArgs a, int first_tile, int owner_launch) {
+    constexpr int L2 = HAS2D ? stage_lds<8, 8>(W) : 0, L1 = HAS1D ? stage_lds<64, 1>(W) : 0;
     __shared__ __align__(16) double smem[(L2 > L1) ? L2 : L1];
     if (blockIdx.x == 0) stage_bookkeeping(a, owner_launch);
-    const int ti = SMALL_SPLIT * first_tile + (a.linear_sched ? (int)blockIdx.x : xcd_chunk(blockIdx.x, gridDim.x));
-    const Tile tile = quarter(ctile(a.tiles, ti / SMALL_SPLIT), ti % SMALL_SPLIT);
+    const int ti = SPLIT * first_tile + (a.linear_sched ? (int)blockIdx.x : xcd_chunk(blockIdx.x, gridDim.x));
+    const Tile tile = quarter(ctile(a.tiles, ti / SPLIT), ti % SPLIT);
     if (HAS1D && tile.kind == 1) {
-        if constexpr (HAS1D) stage_tile<M, NU, 64, 1, NU>(a, ti, tile, smem);
+        if constexpr (HAS1D) stage_tile<M, NU, 64, 1, W>(a, ti, tile, smem);
     } else {
-        if constexpr (HAS2D) stage_tile<M, NU, 8, 8, NU>(a, ti, tile, smem);
+        if constexpr (HAS2D) stage_tile<M, NU, 8, 8, W>(a, ti, tile, smem);
     }
     if (a.stage == 3 && (a.cross ? a.xlast : owner_launch) && blockIdx.x == 0) {
         if (M != DETAILED) step_finish(a);
