@@ -1092,9 +1092,23 @@ janc_status run_steps(janc_ctx* c, janc_plan* P, const janc_time* tm, double* U,
     return JANC_OK;
 }
 
-// A uniform grid whose 32 x 8 tiles are few enough for quarter tiles.
-bool uniform_small(const janc_ctx* c, const janc_grid* g) {
-    return (long long)((g->nx + 31) / 32) * ((g->ny + 7) / 8) <= small_tiles(c->model);
+// Tile width of a uniform grid. Flat grids (ny < 32) take the width whose padded cells, times the
+// cost of a cell at that width, are fewest: 32 x 8 tiles take 1.06 to 1.11 times as long per cell
+// as 16 x 16, 64 x 4 tiles 1.31 to 1.41 times (from 4 species on 1.2, with many tiles). us per
+// step at widths 16 / 32 / 64, 60,000 columns: one-step ny = 3 196 / 130 / 94, 8 207 / 138 / 170,
+// 12 210 / 231 / 228, 16 211 / 235 / 299, 20 367 / 315 / 355, 31 377 / 407 / 530; 9 species ny = 8
+// 437 / 313 / 336, 16 492 / 546 / 588, 20 856 / 789 / 749 (4,000 columns 102 / 98 / 105). Few
+// enough 32 x 8 tiles run as quarter tiles (9 species 1500 x 5: 63 / 48 / 68).
+int uniform_width(const janc_ctx* c, const janc_grid* g) {
+    if (g->ny == 1 || g->ny >= 32 || g->nx < 32) return 16;
+    auto padded = [&](int w) {
+        const int h = 256 / w;
+        return (double)((g->nx + w - 1) / w * w) * ((g->ny + h - 1) / h * h);
+    };
+    if (padded(32) <= 256.0 * small_tiles(c->model)) return 32;
+    const double c16 = padded(16), c32 = 1.1 * padded(32), c64 = 1.35 * padded(64);
+    if (c64 < c16 && c64 < c32) return 64;
+    return c32 < c16 ? 32 : 16;
 }
 
 // Plan of a uniform grid: one domain, one level-0 block covering it; cached.
@@ -1112,8 +1126,7 @@ janc_status uniform_plan(janc_ctx* c, const janc_grid* g, const janc_physics* ph
     janc_plan* P = nullptr;
     janc_status st = build_plan(c, 1, &D, 1, &B, (long long)g->nx * g->ny, 0, &P);
     if (st) return st;
-    if (g->ny > 1 && g->nx >= 64 && g->ny < 16 && !uniform_small(c, g)) P->tile_w = 64;
-    else if (g->ny > 1 && g->nx >= 32 && g->ny < 32) P->tile_w = 32;
+    P->tile_w = uniform_width(c, g);
     st = build_tiles(c, P);
     if (st) {
         plan_free(P);
@@ -1193,8 +1206,7 @@ janc_status run_step_noalloc(janc_ctx* c, const janc_grid* g, const janc_physics
         st = build_plan(c, 1, &D, 1, &B, (long long)g->nx * g->ny, JANC_PLAN_NO_GRAPH, &P, base,
                         (size_t)JANC_NOALLOC_SCRATCH_BYTES);
         if (st) return st;
-        if (g->ny > 1 && g->nx >= 64 && g->ny < 16 && !uniform_small(c, g)) P->tile_w = 64;
-        else if (g->ny > 1 && g->nx >= 32 && g->ny < 32) P->tile_w = 32;
+        P->tile_w = uniform_width(c, g);
         st = build_tiles(c, P);
         if (st) {
             plan_free(P);
