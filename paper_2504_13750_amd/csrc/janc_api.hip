@@ -371,8 +371,6 @@ janc_status build_plan(janc_ctx* c, int nd, const janc_domain* doms, int nb, con
             h.dir[s] = -1;
             if (g.bc[s] == BC_DIRICHLET && (s < 2 || h.twod)) h.dir[s] = ndir++;
         }
-        h.dx0 = g.dx;
-        h.dy0 = g.dy;
         h.idx0 = 1.0 / g.dx;
         h.idy0 = 1.0 / g.dy;
         h.gamma = D.phys.gamma;
@@ -949,7 +947,7 @@ janc_status autotune(janc_ctx* c, janc_plan* P, const janc_time* tm, double* U, 
             a0.Tout = P->T1;   // the entry T solve writes the workspace, not the caller's T
             e = launch_zero_int(P->dstep, s);
             if (e == hipSuccess) e = launch_clear_reduce(base.red, -1, s);
-            if (e == hipSuccess) e = launch_init(c->model, c->ns, P->tile_w, a0, s);
+            if (e == hipSuccess) e = launch_init(c->model, c->ns, a0, s);
             double* Uin[3] = {U, P->U1, P->U2};
             double* Uout[3] = {P->U1, P->U2, P->U1};
             double* Tin[3] = {P->T1, P->T2, P->T1};
@@ -1076,7 +1074,7 @@ janc_status run_steps(janc_ctx* c, janc_plan* P, const janc_time* tm, double* U,
     a0.Tout = T;
     if (!base.cross) {
         HIPCHK(c, launch_clear_reduce(base.red, -1, s), "clear launch");
-        HIPCHK(c, launch_init(c->model, c->ns, P->tile_w, a0, s), "init launch");
+        HIPCHK(c, launch_init(c->model, c->ns, a0, s), "init launch");
     } else {
         // one slot triple per level; each level's entry maxima into its buffer 0
         for (int l = 0; l <= P->maxlev; ++l) {
@@ -1084,7 +1082,7 @@ janc_status run_steps(janc_ctx* c, janc_plan* P, const janc_time* tm, double* U,
             HIPCHK(c, launch_clear_reduce(a0.red, -1, s), "clear launch");
             a0.tiles = P->dtiles + P->lev_first[l];
             a0.ntiles = P->lev_count[l];
-            HIPCHK(c, launch_init(c->model, c->ns, P->tile_w, a0, s), "init launch");
+            HIPCHK(c, launch_init(c->model, c->ns, a0, s), "init launch");
         }
     }
     if (nsteps == 0) return JANC_OK;
@@ -1361,7 +1359,7 @@ janc_status run_adjoint(janc_ctx* c, const janc_grid* g, const janc_physics* ph,
         a0.Uin = U;
         a0.Tin = det ? Tof(U) : T0;
         a0.Tout = det ? Tof(U) : T0;
-        if (e == hipSuccess) e = launch_init(model, ns, P->tile_w, a0, q);
+        if (e == hipSuccess) e = launch_init(model, ns, a0, q);
         return e;
     };
     auto stage = [&](int stn, double* Un, double* Uin, double* Uout, hipStream_t q) -> hipError_t {
@@ -1962,7 +1960,7 @@ janc_status janc_profile_step(janc_ctx* c, janc_plan* P, const janc_time* tm, do
     a0.Uin = U;
     a0.Tin = T;
     a0.Tout = T;
-    HIPCHK(c, launch_init(c->model, c->ns, P->tile_w, a0, s), "init launch");
+    HIPCHK(c, launch_init(c->model, c->ns, a0, s), "init launch");
     hipEvent_t ev[7];
     for (int q = 0; q < 7; ++q) HIPCHK(c, hipEventCreate(&ev[q]), "hipEventCreate");
     const int model = c->model, ns = c->ns;

@@ -535,12 +535,6 @@ __device__ __forceinline__ bool flux_wide(float mu, float mv) {
     return __float_as_uint(mu) + __float_as_uint(mv) >= (2u * 1023u + 58u) << 20;
 }
 
-__device__ __forceinline__ double rk_combine(int stage, double u0, double us, double L, double dt) {
-    if (stage == 1) return u0 + dt * L;
-    if (stage == 2) return 0.75 * u0 + 0.25 * (us + dt * L);
-    return (1.0 / 3.0) * u0 + (2.0 / 3.0) * (us + dt * L);
-}
-
 // dt of domain d for this step from the CFL slot of buffer `bin`; in the crossover
 // advance dt_0, from the largest bound over every level's slot triple.
 __device__ __forceinline__ double step_dt(const StageArgs& a, int d, int bin) {

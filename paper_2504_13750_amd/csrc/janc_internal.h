@@ -33,8 +33,7 @@ struct DevDomain {
     int map_w[MAXL];
     int slot0;                // alpha slot of level 0 (slot0 + level)
     int cfl_slot;             // index of this domain's CFL slot
-    double dx0, dy0;
-    double idx0, idy0;        // 1 / dx0, 1 / dy0
+    double idx0, idy0;        // 1 / dx, 1 / dy of level 0
     double gamma, R, Q, Ea, k;
 };
 
@@ -182,7 +181,7 @@ struct RunShape {
 RunShape run_shape(int model, int cells, int ndom, int cus);
 int run_cap(int cells, bool many);
 hipError_t launch_run(int model, const RunArgs& a, int count, const RunShape& r, hipStream_t s);
-hipError_t launch_init(int model, int ns, int tile_w, const StageArgs& a, hipStream_t s);
+hipError_t launch_init(int model, int ns, const StageArgs& a, hipStream_t s);
 // Tile widths of launch_stage and the halo table that ask for quarter tiles, and for tiles whose
 // valid cells fit into their first quarter.
 constexpr int QUARTER_TILES = 8, TINY_TILES = 1;

@@ -246,7 +246,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs& a, const int ti, con
                                                                        : a.dt[B.domain], -lev)
                                       : (stage == 1) ? step_dt(a, B.domain, 0) : a.dt[B.domain]);
     if (!(dt > 0.0)) return;   // finished domain: state unchanged
-    // 1 / (dx0 / 2^lev): scaling by a power of two is exact
+    // scaling by a power of two is exact
     double idx = uniform(ldexp(D.idx0, lev)), idy = uniform(ldexp(D.idy0, lev));
     const double ax = uniform(slot_get(a.red, bin, 2 * slot));
     const double ay = uniform(slot_get(a.red, bin, 2 * slot + 1));
@@ -1279,7 +1279,7 @@ __global__ __launch_bounds__(1024) void run_kernel(RunArgs A) {
         if (A.dom) take(cdom(A.dom, d));
         else take(A.dom0);
     }
-    const int n = D.nx0, nw = ((int)blockDim.x) >> 6;
+    const int n = D.nx0;
     const long long c = (A.blk ? A.blk[d].offset : 0) + tid;
     const bool own = tid < n;
     // interfaces: group g of m threads takes components g, g + groups, ..

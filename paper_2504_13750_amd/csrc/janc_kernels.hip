@@ -153,8 +153,7 @@ hipError_t launch_run(int model, const RunArgs& a, int count, const RunShape& r,
     return hipGetLastError();
 }
 
-hipError_t launch_init(int model, int ns, int tile_w, const StageArgs& a, hipStream_t s) {
-    (void)tile_w;
+hipError_t launch_init(int model, int ns, const StageArgs& a, hipStream_t s) {
     if (a.ntiles <= 0) return hipSuccess;
     const int per = init_per(a.ntiles), n = (a.ntiles + per - 1) / per;
     if (model == CPG) init_kernel<CPG, 4><<<n, WG, 0, s>>>(a, per);
