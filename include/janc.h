@@ -190,10 +190,11 @@ janc_status janc_step(janc_ctx *ctx, const janc_grid *grid, const janc_physics *
  * 16 (nfields + 1) bytes per cell plus small tables (9 species: about 320 k cells; the
  * one-step model: about 690 k cells); larger grids are rejected with JANC_EINVAL and a
  * message, before any device work. The steps are launched directly; the tables
- * are copied into the array on `stream` at every call. Every call on a device shares that
- * device's array, which keeps the last call's contents: calls that overlap on one device
- * (other streams, other threads, other contexts) race and must be serialized by the
- * caller. */
+ * are copied into the array on `stream` at every call (a one-dimensional grid of at most
+ * 1,023 cells without chemistry, or 704 of the one-step model, takes them with its launch
+ * instead). Every call on a device shares that device's array, which keeps the last call's
+ * contents: calls that overlap on one device (other streams, other threads, other contexts)
+ * race and must be serialized by the caller. */
 janc_status janc_step_noalloc(janc_ctx *ctx, const janc_grid *grid, const janc_physics *phys,
                               const janc_time *time, double *U, double *T, int nsteps,
                               double *t, double *dt_log, void *stream);

@@ -588,9 +588,10 @@ int stage_width(const janc_plan* P) {
 
 // Halo source table: for every tile point outside its block or on a coarse-fine ring,
 // the source resolve() gives (level map, block record, coarser level), found once per
-// plan by a kernel so that the stage launches read one word per such point. Plans of
-// the allocation-free entry point, plans flagged JANC_PLAN_RESOLVE_HALOS and pools of
-// 2^28 cells or more (8 * cell + flags must fit an int) keep resolving in the kernel.
+// plan by a kernel so that the stage launches read one word per such point. Plans
+// flagged JANC_PLAN_RESOLVE_HALOS and pools of 2^28 cells or more (8 * cell + flags must
+// fit an int) keep resolving in the kernel; for the allocation-free entry point only the
+// table's place is found here, if the scratch has room (run_step_noalloc builds it).
 janc_status build_halo_table(janc_ctx* c, janc_plan* P) {
     if (P->dhsrc && !P->arena) hipFree(P->dhsrc);
     P->dhsrc = nullptr;

@@ -25,7 +25,7 @@
 // interface of the 9-species model for 113 when every interface stood alone), and waves
 // that meet at two barriers per tile instead of twelve keep three workgroups per CU
 // apart in phase. 9 species, 1.92 M cells in 661 blocks: 0.305 -> 0.24 ms per stage,
-// 4,225 -> 3,130 VALU instructions per 64 cells; one-step, 131 k cells: 19.1 -> 16.6 us.
+// 4,225 -> 3,080 VALU instructions per 64 cells; one-step, 131 k cells: 19.1 -> 16.6 us.
 // Four workgroups per CU (128 registers) spilled and were slower (0.29 ms).
 // Nothing here is a dense contraction, so there is no MFMA: the work is FP64
 // VALU arithmetic on values staged through LDS.
@@ -1242,7 +1242,7 @@ __global__ void prim_to_cons_kernel(const DevMech* mech, double gamma, double R,
 // wave speeds and dt through LDS. The arithmetic is the stage kernel's (the same functions on
 // the same operands), so the results are bitwise the same.
 // Bound: the latency of a stage's dependent arithmetic and LDS trips, where one launch per
-// stage paid for a launch and a chain of table reads each time (400-cell shock tube: 8.0 -> 4.5
+// stage paid for a launch and a chain of table reads each time (400-cell shock tube: 8.0 -> 4.2
 // us per stage; 10.7 us with 256-cell tiles).
 constexpr int RUN_CELLS = 1023;   // one thread per interface
 
