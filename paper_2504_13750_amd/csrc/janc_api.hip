@@ -633,7 +633,7 @@ janc_status build_tiles(janc_ctx* c, janc_plan* P) {
     P->lev_count.assign(P->maxlev + 1, 0);
     P->kind_mask = 0;
     const int TX = P->tile_w, TY = 256 / TX;
-    bool fits = true;   // every tile's cells fit into its first quarter
+    bool fits = true;   // one tile per block, whose cells fit into its first 8 x 8 or 64 x 1
     for (int l = 0; l <= P->maxlev; ++l) {
         P->lev_first[l] = (int)P->htiles.size();
         for (int id = 0; id < P->nblk; ++id) {
@@ -647,7 +647,7 @@ janc_status build_tiles(janc_ctx* c, janc_plan* P) {
             } else {
                 for (int y = 0; y < h.ny; y += TY)
                     for (int x = 0; x < h.nx; x += TX) P->htiles.push_back(Tile{id, x, y, TX << 8});
-                fits = fits && h.nx <= 8 && h.ny <= 8;
+                fits = fits && h.nx <= 8 && h.ny <= std::min(8, TY);
                 P->kind_mask |= 1;
             }
             P->tile_count[id] = (int)P->htiles.size() - P->tile_first[id];

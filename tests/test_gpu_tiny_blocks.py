@@ -66,3 +66,15 @@ def test_tiny_blocks(model, ns, sizes):
     Uo, To, _, _, _ = oracle.step_blocks(case, Uo, To, 3)
     assert np.all(rel_err(U, Uo) <= TOL), rel_err(U, Uo)
     assert rel_err(T[None], To[None])[0] <= TOL
+
+
+@pytest.mark.parametrize("model,ns", [(MODEL_DETAILED, 3), (MODEL_ONESTEP, 0)])
+@pytest.mark.parametrize("sizes", [[(8, 8), (5, 7), (8, 5), (3, 4)], [(8, 4), (5, 3)]])
+def test_tiny_blocks_at_every_tile_width(model, ns, sizes):
+    """64 x 4 tiles: a block of 5 to 8 rows takes two of them, and a tile of 64 cells at the
+    first would sweep the rows of both; blocks of up to 4 rows take one."""
+    case = ensemble(model, ns, sizes * 20)
+    ref = run_blocks(case, 3)
+    for tile in (32, 64):
+        for a, b in zip(run_blocks(case, 3, tile=tile), ref):
+            assert np.array_equal(a, b), tile
