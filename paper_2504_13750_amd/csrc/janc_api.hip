@@ -80,6 +80,7 @@ struct janc_plan {
     int tile_w = 16;
     bool small = false;           // few tiles: the stages run on quarter tiles (small_tiles)
     bool tiny = false;            // more, of at most 64 cells each in 8 x 8 or 64 x 1
+    bool half = false;            // still more, of at most 128 cells each in 16 x 8 or 128 x 1
     int linear_sched = 0;         // 1: workgroup b takes tile b; 0: XCD-contiguous tile runs
     bool tuned = false;           // janc_plan_autotune has chosen tile_w and linear_sched
     int kind_mask = 0;            // bit 0: 2-D tiles present, bit 1: 1-D tiles present
@@ -583,7 +584,7 @@ StageArgs base_args(janc_plan* P, const janc_time* tm, double* U, double* T, dou
 // (2000 x 1) 26.5 / 23.6, 16 tiles 30 / 26, 64 tiles 31 / 33.
 int small_tiles(int model) { return model == CPG ? 32 : 64; }
 int stage_width(const janc_plan* P) {
-    return P->small ? QUARTER_TILES : P->tiny ? TINY_TILES : P->tile_w;
+    return P->small ? QUARTER_TILES : P->tiny ? TINY_TILES : P->half ? HALF_TILES : P->tile_w;
 }
 
 // Halo source table: for every tile point outside its block or on a coarse-fine ring,
@@ -633,7 +634,9 @@ janc_status build_tiles(janc_ctx* c, janc_plan* P) {
     P->lev_count.assign(P->maxlev + 1, 0);
     P->kind_mask = 0;
     const int TX = P->tile_w, TY = 256 / TX;
-    bool fits = true;   // one tile per block, whose cells fit into its first 8 x 8 or 64 x 1
+    // cells of every tile fit into its first 8 x 8 or 64 x 1 (16 x 8 or 128 x 1); blocks of more
+    // rows than a tile of theirs has do not count, the small tiles would run into the next
+    bool fits = true, hfits = true;
     for (int l = 0; l <= P->maxlev; ++l) {
         P->lev_first[l] = (int)P->htiles.size();
         for (int id = 0; id < P->nblk; ++id) {
@@ -643,11 +646,13 @@ janc_status build_tiles(janc_ctx* c, janc_plan* P) {
             if (!P->hdom[h.domain].twod) {
                 for (int x = 0; x < h.nx; x += 256) P->htiles.push_back(Tile{id, x, 0, 1});
                 fits = fits && h.nx <= 64;
+                hfits = hfits && h.nx <= 128;
                 P->kind_mask |= 2;
             } else {
                 for (int y = 0; y < h.ny; y += TY)
                     for (int x = 0; x < h.nx; x += TX) P->htiles.push_back(Tile{id, x, y, TX << 8});
                 fits = fits && h.nx <= 8 && h.ny <= std::min(8, TY);
+                hfits = hfits && (TX == 16 || h.nx <= 16) && h.ny <= std::min(8, TY);
                 P->kind_mask |= 1;
             }
             P->tile_count[id] = (int)P->htiles.size() - P->tile_first[id];
@@ -656,6 +661,10 @@ janc_status build_tiles(janc_ctx* c, janc_plan* P) {
     }
     P->small = (int)P->htiles.size() <= small_tiles(c->model) && (TX < 64 || !(P->kind_mask & 1));
     P->tiny = !P->small && fits;
+    // Whole / half tiles, us per step (9 species, one-step, gas without chemistry): 300 tiles of
+    // 16 x 8 cells 83 / 93, 42 / 47, 35 / 38; 600 (300 x 20 x 5) 108 / 105, 52 / 49, 43 / 41; 1,000
+    // of 16 x 8 148 / 129, 69 / 58, 57 / 50. Up to two tiles a CU all whole tiles run at once.
+    P->half = !P->small && !P->tiny && hfits && (int)P->htiles.size() > 2 * c->cus;
     if (P->dtiles && !P->arena) hipFree(P->dtiles);
     P->dtiles = nullptr;
     if (janc_status st = pupload(P, &P->dtiles, P->htiles)) return st;

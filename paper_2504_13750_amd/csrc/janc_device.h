@@ -147,15 +147,20 @@ __device__ __forceinline__ void publish_wave3(const Reduce& r, int buf, int i0, 
     }
 }
 
-// The same for values staged in LDS (v[k * 256 + thread], k = 0..2): wave k < 3 takes
-// quantity k of all 256 threads, so that one sixth of the exchanges remain.
+// The same for values that the W waves staged in LDS (v[k * 64 W + thread], k = 0..2): wave k
+// takes quantity k (and k + W) of all threads, so that one sixth of the exchanges remain.
+template <int W>
 __device__ __forceinline__ void publish_staged(const Reduce& r, int buf, int i0, int i1, int i2,
                                                const double* v) {
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
-    if (w >= 3) return;
-    const double* x = v + 256 * w + l;
-    const double m = wave_max(fmax(fmax(x[0], x[64]), fmax(x[128], x[192])));
-    if (l == 0 && m > 0.0) slot_max(r, buf, w == 0 ? i0 : w == 1 ? i1 : i2, m);
+#pragma unroll
+    for (int q = w; q < 3; q += W) {
+        const double* x = v + 64 * W * q + l;
+        double m = fmax(x[0], x[64]);
+        if constexpr (W == 4) m = fmax(m, fmax(x[128], x[192]));
+        m = wave_max(m);
+        if (l == 0 && m > 0.0) slot_max(r, buf, q == 0 ? i0 : q == 1 ? i1 : i2, m);
+    }
 }
 
 // Coarse-fine ring test for block-local cell (li, lj) (segment masks per side).

@@ -183,8 +183,8 @@ int run_cap(int cells, bool many);
 hipError_t launch_run(int model, const RunArgs& a, int count, const RunShape& r, hipStream_t s);
 hipError_t launch_init(int model, int ns, const StageArgs& a, hipStream_t s);
 // Tile widths of launch_stage and the halo table that ask for quarter tiles, and for tiles whose
-// valid cells fit into their first quarter.
-constexpr int QUARTER_TILES = 8, TINY_TILES = 1;
+// valid cells fit into their first quarter or half.
+constexpr int QUARTER_TILES = 8, TINY_TILES = 1, HALF_TILES = 2;
 // Halo source table (row stride: the largest point count of the tile kinds in kind_mask)
 int halo_table_stride(int tile_w, int kind_mask);
 hipError_t launch_halo_table(int tile_w, const StageArgs& a, int* out, int stride, hipStream_t s);

@@ -90,13 +90,14 @@ struct Geom {
 // run each (a round of their own would leave three or two waves idle; workgroups of five
 // waves left the two of each CU that fit resident, half as many waves as four of four).
 constexpr int STAGE_W = 4;
-constexpr int stage_left(int nu) { return nu % STAGE_W <= 2 ? nu % STAGE_W : 0; }
+constexpr int stage_left(int nu, int w) { return 2 * (nu % w) <= w ? nu % w : 0; }
 // Plans of few tiles cut every tile into four of 64 cells (8 x 8, or 64 of a 1-D block), each
 // swept by one wave per component with one interface per lane: a tile's chain of dependent
 // phases is shorter and four times as many CUs work on it, for 2.5 points fetched and 3
 // interfaces formed per cell and direction pair where whole tiles take 1.75 and 2.25. (9
 // species, 128 x 64 cells: 15.5 -> 10 us per stage.)
 constexpr int SMALL_SPLIT = 4;
+constexpr int HALF_W = 2;   // waves of a tile of 128 cells
 
 // LDS doubles of a stage workgroup: u, v, p (detailed model: times SPLIT_SCALE), source and
 // flags (32 bits each) of every point, one split-flux buffer and one word (wide) per wave.
@@ -164,7 +165,7 @@ template <int M, int NU, int TX, int TY, int W>
 __device__ __forceinline__ void stage_tile(const StageArgs& a, const int ti, const Tile tile, double* smem) {
     using G = Geom<TX, TY>;
     constexpr int R = G::R, NPL = G::NPL, NPP = G::NPP;
-    constexpr int LEFT = (R == W && W < NU) ? stage_left(NU) : 0, NR = NU - LEFT;   // components of whole rounds
+    constexpr int LEFT = (R == W && W < NU) ? stage_left(NU, W) : 0, NR = NU - LEFT;   // components of whole rounds
     static_assert(LEFT == 0 || (R == W && 2 * LEFT <= W),
                   "left-over components: one interface of a run per wave, two buffers each");
     static_assert(64 * W >= G::NC && (R == 1 || R == W), "phase 2: wave w has cell w of every run");
@@ -614,10 +615,10 @@ __device__ __forceinline__ void stage_tile(const StageArgs& a, const int ti, con
         if (w == 0) publish_wave3(a.red, bout, i0, i0 + 1, i2, sx, sy, sc);
     } else {
         bufs[tid] = sx;
-        bufs[256 + tid] = sy;
-        bufs[512 + tid] = sc;
+        bufs[64 * W + tid] = sy;
+        bufs[128 * W + tid] = sc;
         __syncthreads();
-        publish_staged(a.red, bout, i0, i0 + 1, i2, bufs);
+        publish_staged<W>(a.red, bout, i0, i0 + 1, i2, bufs);
     }
 }
 
@@ -655,23 +656,28 @@ __device__ __forceinline__ Tile quarter(Tile t, int sub) {
     return t;
 }
 
-// The stage on tiles of 64 cells, W waves each. SPLIT = SMALL_SPLIT: quarter tiles, one wave per
-// component; workgroup b takes quarter b % 4 of tile b / 4. SPLIT = 1: plans of many tiles whose
-// valid cells all fit into the first quarter (blocks of up to 8 x 8 or 64 x 1 cells), four
-// waves, as many workgroups as a CU holds; the whole tiles sweep 256 cells for at most 64 of
+// The stage on tiles of 8 x 8 or 64 x 1 cells, W waves each. SPLIT = SMALL_SPLIT: quarter tiles,
+// one wave per component; workgroup b takes quarter b % 4 of tile b / 4. SPLIT = 1: plans of many
+// tiles whose valid cells all fit into the first quarter (blocks of up to 8 x 8 or 64 x 1 cells),
+// four waves, as many workgroups as a CU holds; the whole tiles sweep 256 cells for at most 64 of
 // them (us per step, whole / these: 9 species 1000 x 50 cells 105 / 75, 4000 x 8 x 8 446 / 287, 3
 // species 4000 x 50 167 / 115, one-step 4000 x 8 x 8 211 / 124).
+// Two waves: tiles of 16 x 8 or 128 x 1 cells (runs of two interfaces per lane), for plans of
+// still more tiles whose valid cells fit into the first half (whole / these: 9 species 4000 x 100
+// cells 350 / 276, 4000 x 20 x 5 837 / 623, 3 species 4000 x 100 184 / 135, one-step 4000 x 20 x
+// 5 372 / 279, gas without chemistry 301 / 226).
 template <int M, int NU, int W, int SPLIT, bool HAS1D, bool HAS2D>
 __global__ __launch_bounds__(64 * W) void stage_small_kernel(StageArgs a, int first_tile, int owner_launch) {
-    constexpr int L2 = HAS2D ? stage_lds<8, 8>(W) : 0, L1 = HAS1D ? stage_lds<64, 1>(W) : 0;
+    constexpr int TX = W == HALF_W ? 16 : 8, N1 = 8 * TX;
+    constexpr int L2 = HAS2D ? stage_lds<TX, 8>(W) : 0, L1 = HAS1D ? stage_lds<N1, 1>(W) : 0;
     __shared__ __align__(16) double smem[(L2 > L1) ? L2 : L1];
     if (blockIdx.x == 0) stage_bookkeeping(a, owner_launch);
     const int ti = SPLIT * first_tile + (a.linear_sched ? (int)blockIdx.x : xcd_chunk(blockIdx.x, gridDim.x));
     const Tile tile = quarter(ctile(a.tiles, ti / SPLIT), ti % SPLIT);
     if (HAS1D && tile.kind == 1) {
-        if constexpr (HAS1D) stage_tile<M, NU, 64, 1, W>(a, ti, tile, smem);
+        if constexpr (HAS1D) stage_tile<M, NU, N1, 1, W>(a, ti, tile, smem);
     } else {
-        if constexpr (HAS2D) stage_tile<M, NU, 8, 8, W>(a, ti, tile, smem);
+        if constexpr (HAS2D) stage_tile<M, NU, TX, 8, W>(a, ti, tile, smem);
     }
     if (a.stage == 3 && (a.cross ? a.xlast : owner_launch) && blockIdx.x == 0) {
         if (M != DETAILED) step_finish(a);

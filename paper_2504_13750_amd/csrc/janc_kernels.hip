@@ -15,12 +15,13 @@ __global__ void zero_int_kernel(int* p) {
     if (threadIdx.x == 0) *p = 0;
 }
 
+template <int TX>
 __global__ __launch_bounds__(WG) void halo_table_small_kernel(StageArgs a, int* out, int stride, int split) {
     const int ti = blockIdx.x;
     const Tile tile = quarter(a.tiles[ti / split], ti % split);
     int* row = out + (size_t)ti * stride;
-    if (tile.kind == 1) halo_table_tile<64, 1>(a, ti, tile, row);
-    else halo_table_tile<8, 8>(a, ti, tile, row);
+    if (tile.kind == 1) halo_table_tile<8 * TX, 1>(a, ti, tile, row);
+    else halo_table_tile<TX, 8>(a, ti, tile, row);
 }
 
 // ------------------------------------------------------------------ launchers
@@ -85,6 +86,7 @@ hipError_t launch_stage(int model, int ns, int kind_mask, int tile_w, const Stag
 
 int halo_table_stride(int tile_w, int kind_mask) {
     if (tile_w == QUARTER_TILES || tile_w == TINY_TILES) return (kind_mask & 1) ? Geom<8, 8>::NP : Geom<64, 1>::NP;
+    if (tile_w == HALF_TILES) return (kind_mask & 1) ? Geom<16, 8>::NP : Geom<128, 1>::NP;
     int np2 = Geom<16, 16>::NP;
     if (tile_w == 32) np2 = Geom<32, 8>::NP;
     else if (tile_w == 64) np2 = Geom<64, 4>::NP;
@@ -96,8 +98,9 @@ int halo_table_stride(int tile_w, int kind_mask) {
 
 hipError_t launch_halo_table(int tile_w, const StageArgs& a, int* out, int stride, hipStream_t s) {
     if (a.ntiles <= 0) return hipSuccess;
-    if (tile_w == QUARTER_TILES) halo_table_small_kernel<<<SMALL_SPLIT * a.ntiles, WG, 0, s>>>(a, out, stride, SMALL_SPLIT);
-    else if (tile_w == TINY_TILES) halo_table_small_kernel<<<a.ntiles, WG, 0, s>>>(a, out, stride, 1);
+    if (tile_w == QUARTER_TILES) halo_table_small_kernel<8><<<SMALL_SPLIT * a.ntiles, WG, 0, s>>>(a, out, stride, SMALL_SPLIT);
+    else if (tile_w == TINY_TILES) halo_table_small_kernel<8><<<a.ntiles, WG, 0, s>>>(a, out, stride, 1);
+    else if (tile_w == HALF_TILES) halo_table_small_kernel<16><<<a.ntiles, WG, 0, s>>>(a, out, stride, 1);
     else if (tile_w == 32) halo_table_kernel<32, 8><<<a.ntiles, WG, 0, s>>>(a, out, stride);
     else if (tile_w == 64) halo_table_kernel<64, 4><<<a.ntiles, WG, 0, s>>>(a, out, stride);
     else halo_table_kernel<16, 16><<<a.ntiles, WG, 0, s>>>(a, out, stride);

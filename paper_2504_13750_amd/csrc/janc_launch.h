@@ -24,6 +24,7 @@ hipError_t launch_stage_m(int kind_mask, int tile_w, const StageArgs& a, int fir
     } while (0)
     if (tile_w == QUARTER_TILES) JANC_SMALL(NU, SMALL_SPLIT);
     else if (tile_w == TINY_TILES) JANC_SMALL(STAGE_W, 1);
+    else if (tile_w == HALF_TILES) JANC_SMALL(HALF_W, 1);
     else if (tile_w == 32) JANC_STAGE(32, 8);
     else if (tile_w == 64) JANC_STAGE(64, 4);
     else JANC_STAGE(16, 16);
